@@ -110,8 +110,8 @@ size_t plan_buffer_bytes(int nside, int lmax, int dtype, int nmaps) {
   return b;
 }
 
-// Device bytes of the shared tables of one (nside, lmax) geometry.
-size_t geometry_bytes(int nside, int lmax) {
+// Device bytes of the shared tables of one (nside, lmax) geometry (fp64: with the FP64 Legendre tables).
+size_t geometry_bytes(int nside, int lmax, bool fp64) {
   const size_t nalm = (size_t)(lmax + 1) * (lmax + 2) / 2;
   const size_t rows = nalm + (size_t)(lmax + 1) * ROW_PAD;
   size_t blue = 0;
@@ -121,8 +121,13 @@ size_t geometry_bytes(int nside, int lmax) {
       while (M < (size_t)(8 * i - 1)) M <<= 1;
       blue += M + 4 * i;
     }
+  // FP64 Legendre tables: factors per row, and a start state per ring pair of every work item (at
+  // most one analysis item per (m, block) and 32 l, two per wave of a full launch beyond that)
+  const size_t items = std::min<size_t>(5 * nalm / 16, (size_t)(lmax + 1) * ((nside + 127) / 128) + 8192) +
+                       (size_t)(lmax + 1) * ((nside + 127) / 128);
+  const size_t leg64 = fp64 ? rows * 40 + items * std::min(2 * nside + 63, 256) * 17 : 0;
   return 2 * rows * 8 + blue * 24 + (size_t)(lmax + 1) * 64 + (size_t)(16 * nside + 64) * 24 +
-         5 * nalm + 256 * 1024;
+         5 * nalm + leg64 + 256 * 1024;
 }
 
 }  // namespace mwf
@@ -328,7 +333,7 @@ int run_analysis(wf_plan_s* p, hipStream_t s, int nmaps) {
   if (p->dtype != WF_F64) {
     TIMED(1, if (int rc = launch_mfma_ana(p, p->tune, nmaps, s)) return rc);
   } else {
-    TIMED(1, MWF_HIP(launch_legendre_analysis_f64(p->dev, g.items_ana, g.bins_ana, g.nbins_ana, nmaps,
+    TIMED(1, MWF_HIP(launch_legendre_analysis_f64(p->dev, g.leg64, nmaps,
                                                   static_cast<const double*>(p->G), p->partial, s)));
   }
   return WF_OK;
@@ -360,8 +365,8 @@ int run_synthesis(wf_plan_s* p, hipStream_t s, int mode, int nmaps, double lam, 
   a.chi2 = chi2;
   a.chi2_stride = (int64_t)CHI_REC * p->chi2_cap;
   TIMED(2, {
-    MWF_HIP(launch_legendre_coeff(p->dev, a, s));
-    if (mode != SY_ALM_ONLY) MWF_HIP(launch_legendre_synthesis_f64(p->dev, g.items_syn, g.bins_syn, g.nbins_syn, a, s));
+    MWF_HIP(launch_legendre_coeff(p->dev, g.leg64, a, s));
+    if (mode != SY_ALM_ONLY) MWF_HIP(launch_legendre_synthesis_f64(p->dev, g.leg64, a, s));
   });
   return WF_OK;
 }
@@ -430,7 +435,6 @@ int plan_alloc(wf_plan_s* p) {
   D.tau = p->tau;
   D.omega = g.omega;
   D.ring_block_ana = g.ring_block_ana;
-  D.ring_block_syn = g.ring_block_syn;
   D.nblk_max = g.nblk_max_ana;
   D.pairs = g.pairs;
   D.q = p->q;
@@ -479,7 +483,7 @@ int wf_footprint(int32_t nside, int32_t lmax, int32_t dtype, int32_t nmaps, size
   if (nmaps < 1) return fail(WF_EINVAL, "nmaps must be >= 1");
   if (!valid_dtype(dtype)) return fail(WF_EINVAL, "unknown dtype");
   if (int rc = validate_shape(nside, lmax)) return rc;
-  *bytes = geometry_bytes(nside, lmax) + plan_buffer_bytes(nside, lmax, dtype, nmaps);
+  *bytes = geometry_bytes(nside, lmax, dtype == WF_F64) + plan_buffer_bytes(nside, lmax, dtype, nmaps);
   return WF_OK;
 }
 
@@ -529,7 +533,7 @@ int wf_plan(wf_plan_t* out, int32_t nside, int32_t lmax, const double* cl, const
   if (!(nmax > 0)) return fail(WF_EINVAL, "no observed pixel (all ninv == 0 or masked)");
 
   std::shared_ptr<Geometry> geo;
-  if (int rc = get_geometry(nside, lmax, &geo)) return rc;
+  if (int rc = get_geometry(nside, lmax, dtype == WF_F64, &geo)) return rc;
   auto* p = new wf_plan_s();
   auto bail = [&](int code) {
     wf_destroy(p);
@@ -724,7 +728,7 @@ int band_plan(wf_plan_s* p, int L, wf_plan_s** out) {
     return WF_OK;
   }
   std::shared_ptr<Geometry> geo;
-  if (int rc = get_geometry(p->geo->nside, L, &geo)) return rc;
+  if (int rc = get_geometry(p->geo->nside, L, p->dtype == WF_F64, &geo)) return rc;
   auto* b = new wf_plan_s();
   b->geo = geo;
   b->dtype = p->dtype;

@@ -59,6 +59,52 @@ std::mutex g_geo_mu;
 // Weak entries: the tables of a shape live while a plan or serving lane holds them.
 std::map<std::tuple<int, int, int>, std::weak_ptr<Geometry>> g_geo;
 
+// Runs the reach kernel of a geometry whose recurrence tables are on the device (see launch_reach).
+int run_reach(const Geometry& g, std::vector<uint16_t>* wake, std::vector<uint16_t>* rise) {
+  PlanDev D{};
+  D.nside = g.nside;
+  D.lmax = g.lmax;
+  D.npairs = g.npairs;
+  D.pairs = g.pairs;
+  D.A = g.A;
+  D.row_off = g.row_off;
+  D.norm_m = g.norm;
+  const size_t n = (size_t)(g.lmax + 1) * g.npairs;
+  uint16_t *dw = nullptr, *dr = nullptr;
+  DevMem tmp;
+  int rc;
+  if ((rc = tmp.alloc(&dw, n)) || (rc = tmp.alloc(&dr, n))) return rc;
+  MWF_HIP(launch_reach(D, dw, dr, nullptr));
+  if (wake) {
+    wake->resize(n);
+    MWF_HIP(hipMemcpy(wake->data(), dw, n * sizeof(uint16_t), hipMemcpyDeviceToHost));
+  }
+  if (rise) {
+    rise->resize(n);
+    MWF_HIP(hipMemcpy(rise->data(), dr, n * sizeof(uint16_t), hipMemcpyDeviceToHost));
+  }
+  return WF_OK;
+}
+
+// Work items (m, block of rb ring pairs) over the active pairs of every m, largest first.
+std::vector<WorkItem> items_by_size(const Geometry& g, int rb) {
+  const int lmax = g.lmax;
+  std::vector<WorkItem> items;
+  for (int m = 0; m <= lmax; ++m) {
+    const int nb = (g.n_active[m] + rb - 1) / rb;
+    for (int b = 0; b < nb; ++b) items.push_back({m, b});
+  }
+  std::stable_sort(items.begin(), items.end(), [&](const WorkItem& a, const WorkItem& b) {
+    auto c = [&](const WorkItem& w) {
+      const int rings = std::min(rb, g.n_active[w.m] - w.blk * rb);
+      return (double)(lmax - w.m + 1) * (double)std::max(rings, 1);
+    };
+    return c(a) > c(b);
+  });
+  if (items.empty()) items.push_back({0, 0});
+  return items;
+}
+
 int build_geometry(Geometry& g) {
   const int nside = g.nside, lmax = g.lmax;
   g.npix = 12LL * nside * nside;
@@ -186,20 +232,22 @@ int build_geometry(Geometry& g) {
         return sqrtl((4.0L * l * l - 1.0L) / ((long double)(l - m) * (long double)(l + m)));
       };
       const int64_t r = row_off[m];
-      long double c_lm2 = 1.0L, c_lm1 = 1.0L;
+      long double c_lm2 = 1.0L, c_lm1 = 1.0L, alm1 = 0.0L;
       A[r] = 0.0;
       C[r] = 1.0;
       if (m + 1 <= lmax) {
-        A[r + 1] = (double)alpha(m + 1);
+        alm1 = alpha(m + 1);
+        A[r + 1] = (double)alm1;
         C[r + 1] = 1.0;
       }
       for (int l = m + 2; l <= lmax; ++l) {
-        const long double al = alpha(l), alm1 = alpha(l - 1);
+        const long double al = alpha(l);
         const long double cl_ = c_lm2 * al / alm1;
         A[r + (l - m)] = (double)(al * c_lm1 / cl_);
         C[r + (l - m)] = (double)cl_;
         c_lm2 = c_lm1;
         c_lm1 = cl_;
+        alm1 = al;
       }
     }
   }
@@ -282,23 +330,9 @@ int build_geometry(Geometry& g) {
   }
 
   // ---- polar skip: ring pairs whose lambda_lm never leaves the negligible range
-  PlanDev D{};
-  D.nside = nside;
-  D.lmax = lmax;
-  D.npairs = g.npairs;
-  D.pairs = g.pairs;
-  D.A = g.A;
-  D.C = g.C;
-  D.row_off = g.row_off;
-  D.row_m = g.row_m;
-  D.norm_m = g.norm;
-  std::vector<uint16_t> wake((size_t)(lmax + 1) * g.npairs);
   {
-    uint16_t* d_wake = nullptr;
-    DevMem tmp;
-    if ((rc = tmp.alloc(&d_wake, wake.size()))) return rc;
-    MWF_HIP(launch_reach(D, d_wake, nullptr));
-    MWF_HIP(hipMemcpy(wake.data(), d_wake, wake.size() * sizeof(uint16_t), hipMemcpyDeviceToHost));
+    std::vector<uint16_t> wake;
+    if ((rc = run_reach(g, &wake, nullptr))) return rc;
     g.n_active.assign(lmax + 1, 0);
     g.units_active = 0;
     for (int m = 0; m <= lmax; ++m) {
@@ -309,34 +343,7 @@ int build_geometry(Geometry& g) {
       g.units_active += (int64_t)na * (lmax - m + 1);
     }
   }
-  // estimated cost of an FP64 work item of rb ring pairs, in steps of l: steps with a
-  // still-scaled ring in the block take the rescale path of every chunk
-  auto item_cost = [&](const WorkItem& w, int rb, int scaled_cost) {
-    const int nl = lmax - w.m + 1;
-    int scaled = 0;
-    const int q1 = std::min(g.n_active[w.m], (w.blk + 1) * rb);
-    for (int q = w.blk * rb; q < q1; ++q) {
-      const uint16_t wk = wake[(size_t)w.m * g.npairs + q];
-      if (wk != WAKE_NEVER) scaled = std::max(scaled, std::min((int)wk, nl));
-    }
-    return (int64_t)4 * (nl - scaled) + (int64_t)scaled_cost * scaled + 4 * FP64_ITEM_COST_L;
-  };
-  auto make_items = [&](int rb) {
-    std::vector<WorkItem> items;
-    for (int m = 0; m <= lmax; ++m) {
-      const int nb = (g.n_active[m] + rb - 1) / rb;
-      for (int b = 0; b < nb; ++b) items.push_back({m, b});
-    }
-    std::stable_sort(items.begin(), items.end(), [&](const WorkItem& a, const WorkItem& b) {
-      auto c = [&](const WorkItem& w) {
-        const int rings = std::min(rb, g.n_active[w.m] - w.blk * rb);
-        return (double)(lmax - w.m + 1) * (double)std::max(rings, 1);
-      };
-      return c(a) > c(b);
-    });
-    if (items.empty()) items.push_back({0, 0});
-    return items;
-  };
+  auto make_items = [&](int rb) { return items_by_size(g, rb); };
   // Matrix-core lists, ordered for the L2 caches of the XCDs. A row of G or F holds the
   // entries of consecutive m side by side (16 bytes each in FP32), so the items of one ring
   // block and eight consecutive m read or write the same one or two 128-byte lines of every
@@ -366,60 +373,240 @@ int build_geometry(Geometry& g) {
           out.push_back(g < groups.size() && k < groups[g].size() ? groups[g][k] : WorkItem{-1, 0});
     return out;
   };
-  // FP64 lists: one bin per wave of a launch (FP64_WAVES_PER_SIMD per SIMD, at most one
-  // per item); items, most costly first, each go to the least-loaded bin; bins are
-  // stored in turn, with off[b] .. off[b + 1] the items of bin b
-  auto pack_bins = [&](int rb, int scaled_cost, std::vector<int32_t>* off) {
-    std::vector<WorkItem> items = make_items(rb);
-    std::vector<int64_t> cost(items.size());
-    for (size_t i = 0; i < items.size(); ++i) cost[i] = item_cost(items[i], rb, scaled_cost);
-    std::vector<int> order(items.size());
-    for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-    const int nb = std::max(1, std::min((int)items.size(), FP64_WAVES_PER_SIMD * 4 * g.n_cu));
-    std::vector<std::vector<int>> bins(nb);
-    using Load = std::pair<int64_t, int>;
-    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> least;
-    for (int b = 0; b < nb; ++b) least.push({0, b});
-    for (int i : order) {
-      const Load l = least.top();
-      least.pop();
-      bins[l.second].push_back(i);
-      least.push({l.first + cost[i], l.second});
-    }
-    std::vector<WorkItem> packed;
-    off->assign(1, 0);
-    for (const auto& b : bins) {
-      for (int i : b) packed.push_back(items[i]);
-      off->push_back((int32_t)packed.size());
-    }
-    return packed;
-  };
   g.ring_block_ana = ana_ring_block(g.npairs);
-  g.ring_block_syn = ana_ring_block(g.npairs);
   g.nblk_max_ana = (g.npairs + g.ring_block_ana - 1) / g.ring_block_ana;
   std::vector<int32_t> nblk(lmax + 1);
   for (int m = 0; m <= lmax; ++m) nblk[m] = (g.n_active[m] + g.ring_block_ana - 1) / g.ring_block_ana;
-  std::vector<int32_t> bins_ana, bins_syn;
-  const auto ia = pack_bins(g.ring_block_ana, FP64_SCALED_COST_ANA, &bins_ana);
-  const auto is = pack_bins(g.ring_block_syn, FP64_SCALED_COST_SYN, &bins_syn);
   const auto i128 = xcd_order(make_items(128)), i256 = xcd_order(make_items(256)), i64 = xcd_order(make_items(64));
-  g.n_ana = (int)ia.size();
-  g.n_syn = (int)is.size();
-  g.nbins_ana = (int)bins_ana.size() - 1;
-  g.nbins_syn = (int)bins_syn.size() - 1;
   g.n_a128 = (int)i128.size();
   g.n_a256 = (int)i256.size();
   g.n_s64 = (int)i64.size();
   if ((rc = M.upload(&g.nact, g.n_active))) return rc;
   if ((rc = M.upload(&g.nblk_ana, nblk))) return rc;
-  if ((rc = M.upload(&g.items_ana, ia))) return rc;
-  if ((rc = M.upload(&g.items_syn, is))) return rc;
-  if ((rc = M.upload(&g.bins_ana, bins_ana))) return rc;
-  if ((rc = M.upload(&g.bins_syn, bins_syn))) return rc;
   if ((rc = M.upload(&g.items_a128, i128))) return rc;
   if ((rc = M.upload(&g.items_a256, i256))) return rc;
   if ((rc = M.upload(&g.items_s64, i64))) return rc;
+  return WF_OK;
+}
+
+// Packs items (with their costs) into the workgroups of a launch, one per CU: items, most costly
+// first, each go to the least-loaded workgroup, which keeps that order. Small lists take as
+// many waves per workgroup as give every CU work. off: the item range of each workgroup.
+// In a full launch the items of eight consecutive m go to the workgroups of one XCD (workgroup b
+// runs on XCD b mod 8): their 32-byte entries of G and F share 128-byte lines, which then are
+// fetched into one L2 and written back from one (Nside 512: analysis 107 -> 102 us, synthesis
+// 75 -> 69 us).
+std::vector<Item64> pack_items(const std::vector<Item64>& items, const std::vector<int64_t>& cost, int n_cu,
+                               int max_waves, std::vector<int32_t>* off, int* waves) {
+  int W = 1;
+  while (W < max_waves && (int64_t)W * n_cu < (int64_t)items.size()) W = std::min(2 * W, max_waves);
+  const int nwg = std::max(1, std::min(n_cu, (int)((items.size() + W - 1) / W)));
+  const int nx = nwg % 8 == 0 && nwg >= 64 ? 8 : 1;
+  // least-loaded dealing of ids (in the order given, with their loads) to n places
+  auto deal = [](const std::vector<int>& ids, const std::vector<int64_t>& load, int n) {
+    std::vector<std::vector<int>> to(n);
+    using Load = std::pair<int64_t, int>;
+    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> least;
+    for (int b = 0; b < n; ++b) least.push({0, b});
+    for (int i : ids) {
+      const Load l = least.top();
+      least.pop();
+      to[l.second].push_back(i);
+      least.push({l.first + load[i], l.second});
+    }
+    return to;
+  };
+  auto by_load = [](const std::vector<int64_t>& load) {
+    std::vector<int> order(load.size());
+    for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return load[a] > load[b]; });
+    return order;
+  };
+  std::vector<int64_t> group;
+  for (size_t i = 0; i < items.size(); ++i) {
+    const size_t g = items[i].m / 8;
+    if (g >= group.size()) group.resize(g + 1, 0);
+    group[g] += cost[i];
+  }
+  std::vector<int> xcd(group.size(), 0);
+  if (nx > 1) {
+    const auto to = deal(by_load(group), group, nx);
+    for (int x = 0; x < nx; ++x)
+      for (int g : to[x]) xcd[g] = x;
+  }
+  std::vector<std::vector<int>> ids(nx);
+  for (int i : by_load(cost)) ids[xcd[items[i].m / 8]].push_back(i);
+  std::vector<std::vector<std::vector<int>>> to(nx);
+  for (int x = 0; x < nx; ++x) to[x] = deal(ids[x], cost, nwg / nx);
+  std::vector<Item64> packed;
+  off->assign(1, 0);
+  for (int b = 0; b < nwg; ++b) {
+    for (int i : to[b % nx][b / nx]) packed.push_back(items[i]);
+    off->push_back((int32_t)packed.size());
+  }
+  *waves = W;
+  return packed;
+}
+
+// Tables and work lists of the FP64 Legendre kernels (Leg64Dev), made for the first FP64
+// plan of the shape; recurrence and factors as derived in phase_a.hip.
+int build_leg64(Geometry& g) {
+  const int lmax = g.lmax, nbm = g.nblk_max_ana;
+  std::vector<double> ab[3];             // by form: MID, EQ, CAP
+  for (auto& t : ab) t.assign(g.rows_total, 0.0);
+  std::vector<double2> co(g.rows_total, make_double2(0.0, 0.0));
+  {
+    std::vector<long double> eps(lmax + 2), c((size_t)lmax / 2 + 2);
+    int64_t off = 0;
+    for (int m = 0; m <= lmax; ++m) {
+      const int nl = lmax - m + 1;
+      // eps_l at index l - m, l = m .. lmax + 1
+      for (int i = 0; i <= nl; ++i)
+        eps[i] = sqrtl((long double)i * (2.0L * m + i) / (4.0L * (m + i) * (m + i) - 1.0L));
+      eps[0] = 0.0L;
+      c[0] = 1.0L / eps[1];
+      co[off] = make_double2(1.0, 0.0);       // eps_{m+1} c_0
+      if (nl > 1) co[off + 1] = make_double2((double)c[0], 0.0);
+      for (int k = 1; 2 * k < nl; ++k) {
+        const int i = 2 * k;                   // l - m of the even function; u_k = (a z^2 + b) u_{k-1} - u_{k-2}
+        const long double w = eps[i] * eps[i + 1];
+        c[k] = k == 1 ? c[0] : c[k - 2] * eps[i - 1] * eps[i - 2] / w;
+        const long double a = c[k - 1] / (c[k] * w);
+        const long double b = -a * (eps[i] * eps[i] + eps[i - 1] * eps[i - 1]);
+        ab[0][off + i] = (double)a;
+        ab[0][off + i + 1] = (double)b;
+        ab[1][off + i] = ab[2][off + i] = (double)-a;
+        ab[1][off + i + 1] = (double)-(b + 2.0L);
+        ab[2][off + i + 1] = (double)(a + b - 2.0L);
+        co[off + i] = make_double2((double)(eps[i + 1] * c[k]), (double)(eps[i] * c[k - 1]));
+        if (i + 1 < nl) co[off + i + 1] = make_double2((double)c[k], 0.0);
+      }
+      off += nl + ROW_PAD;
+    }
+  }
+  // (m, block of rb pairs) with the first l - m, in chunks of 16, at which a ring pair of it exceeds
+  // 2^-128, and the l - m up to which a ring of it is still scaled
+  std::vector<uint16_t> wake, rise;
+  if (int rc = run_reach(g, &wake, &rise)) return rc;
+  struct Block {
+    int m, blk, first, scaled;
+  };
+  auto blocks = [&](int rb) {
+    std::vector<Block> out;
+    for (int m = 0; m <= lmax; ++m)
+      for (int b = 0; b * rb < g.n_active[m]; ++b) {
+        const int nl = lmax - m + 1, q1 = std::min(g.n_active[m], (b + 1) * rb);
+        int first = nl, scaled = 0;
+        for (int q = b * rb; q < q1; ++q) {
+          const size_t at = (size_t)m * g.npairs + q;
+          if (rise[at] != WAKE_NEVER) first = std::min(first, (int)rise[at] / CHUNK * CHUNK);
+          if (wake[at] != WAKE_NEVER) scaled = std::max(scaled, std::min((int)wake[at], nl));
+        }
+        out.push_back({m, b, first, scaled});
+      }
+    return out;
+  };
+  auto item_cost = [&](const Item64& w, int scaled, int scaled_cost) {
+    const int64_t n = w.i1 - w.i0, sc = std::min<int64_t>(n, std::max(0, scaled - w.i0));
+    return 4 * (n - sc) + scaled_cost * sc + 4 * FP64_ITEM_COST_L;
+  };
+  const auto whole = blocks(g.ring_block_ana);
+  // analysis: the l of a block in parts of about half a wave's share, 32 at least (in chunks of 16)
+  std::vector<int32_t> start((size_t)(lmax + 1) * nbm);
+  std::vector<Item64> items;
+  std::vector<int64_t> cost;
+  {
+    for (int m = 0; m <= lmax; ++m)
+      for (int b = 0; b < nbm; ++b) start[(size_t)m * nbm + b] = lmax - m + 1;
+    int64_t total = 0;
+    for (const Block& b : whole) total += lmax - b.m + 1 - b.first;
+    const int64_t part = std::max<int64_t>(32, (total / (2 * FP64_ANA_WAVES * g.n_cu) + CHUNK - 1) / CHUNK * CHUNK);
+    for (const Block& b : whole) {
+      start[(size_t)b.m * nbm + b.blk] = b.first;
+      const int nl = lmax - b.m + 1, n = nl - b.first;
+      if (n == 0) continue;
+      const int parts = std::max(1, (int)((n + part / 2) / part));
+      const int len = ((n + parts - 1) / parts + CHUNK - 1) / CHUNK * CHUNK;
+      for (int i = b.first; i < nl; i += len) {
+        const Item64 w{b.m, b.blk, i, std::min(nl, i + len)};
+        items.push_back(w);
+        cost.push_back(item_cost(w, b.scaled, FP64_SCALED_COST_ANA));
+      }
+    }
+  }
+  std::vector<int32_t> wg_ana, wg_syn;
+  int waves_ana = 1, waves_syn = 1;
+  const auto ia = pack_items(items, cost, g.n_cu, FP64_ANA_WAVES, &wg_ana, &waves_ana);
+  // synthesis: the largest blocks, up to 256 pairs, that still give every wave of a full launch an
+  // item and a half (a wave's share is then not set by its longest item). A smaller block that
+  // never rises inside one of the analysis's that does gets an item of no steps, which writes
+  // zeros: the entries of F that a plan writes then grow with its band limit, and the others,
+  // zero from the start, stay so when the coefficients of a truncated sweep are carried over.
+  int rb_syn = g.ring_block_ana;
+  for (;; rb_syn /= 2) {
+    const auto bl = blocks(rb_syn);
+    items.clear();
+    cost.clear();
+    for (const Block& b : bl) {
+      const int nl = lmax - b.m + 1;
+      if (start[(size_t)b.m * nbm + b.blk * rb_syn / g.ring_block_ana] >= nl) continue;
+      const Item64 w{b.m, b.blk, b.first, nl};
+      items.push_back(w);
+      cost.push_back(item_cost(w, b.scaled, FP64_SCALED_COST_SYN));
+    }
+    if (rb_syn == LANES || (int64_t)items.size() * 2 >= (int64_t)FP64_SYN_WAVES * g.n_cu * 3) break;
+  }
+  const auto is = pack_items(items, cost, g.n_cu, FP64_SYN_WAVES, &wg_syn, &waves_syn);
+  std::vector<double> z(g.npairs);
+  for (int q = 0; q < g.npairs; ++q) z[q] = ring_geometry(g.nside, 2 * g.nside - q).z;
+
+  DevMem& M = g.mem;
+  double *dab[3] = {}, *dz = nullptr;
+  double2* dco = nullptr;
+  int32_t* dstart = nullptr;
+  int rc;
+  if ((rc = M.upload(&dab[0], ab[0])) || (rc = M.upload(&dab[1], ab[1])) || (rc = M.upload(&dab[2], ab[2])) ||
+      (rc = M.upload(&dco, co)) || (rc = M.upload(&dz, z)) || (rc = M.upload(&dstart, start)))
+    return rc;
+  Leg64Dev L{};
+  for (int f = 0; f < 3; ++f) L.ab[f] = dab[f];
+  L.co = dco;
+  L.z = dz;
+  L.start = dstart;
+  PlanDev D{};
+  D.nside = g.nside;
+  D.lmax = lmax;
+  D.npairs = g.npairs;
+  D.pairs = g.pairs;
+  D.row_off = g.row_off;
+  D.norm_m = g.norm;
+  D.n_active = g.nact;
+  auto make_list = [&](Leg64List& T, const std::vector<Item64>& it, const std::vector<int32_t>& wg, int waves,
+                       int rb) -> int {
+    Item64* di = nullptr;
+    int32_t* db = nullptr;
+    double2* ds = nullptr;
+    uint8_t* dc = nullptr;
+    int rc;
+    if ((rc = M.upload(&di, it)) || (rc = M.upload(&db, wg)) || (rc = M.alloc(&ds, it.size() * rb)) ||
+        (rc = M.alloc(&dc, it.size() * rb)))
+      return rc;
+    T.items = di;
+    T.wg = db;
+    T.nwg = (int)wg.size() - 1;
+    T.waves = waves;
+    T.rb = rb;
+    MWF_HIP(launch_start_state(D, L, T, (int)it.size(), CHUNK, ds, dc, nullptr));
+    T.state = ds;
+    T.scale = dc;
+    return WF_OK;
+  };
+  if ((rc = make_list(L.ana, ia, wg_ana, waves_ana, g.ring_block_ana)) ||
+      (rc = make_list(L.syn, is, wg_syn, waves_syn, rb_syn)))
+    return rc;
+  MWF_HIP(hipStreamSynchronize(nullptr));
+  g.leg64 = L;
+  g.leg64_ready = true;
   return WF_OK;
 }
 
@@ -451,7 +638,7 @@ RingGeo ring_geometry(int n, int i) {
   return g;
 }
 
-int get_geometry(int nside, int lmax, std::shared_ptr<Geometry>* out) {
+int get_geometry(int nside, int lmax, bool fp64, std::shared_ptr<Geometry>* out) {
   int dev = 0;
   MWF_HIP(hipGetDevice(&dev));
   const auto key = std::make_tuple(dev, nside, lmax);
@@ -459,6 +646,8 @@ int get_geometry(int nside, int lmax, std::shared_ptr<Geometry>* out) {
   auto it = g_geo.find(key);
   if (it != g_geo.end()) {
     if (auto live = it->second.lock()) {
+      if (fp64 && !live->leg64_ready)
+        if (int rc = build_leg64(*live)) return rc;
       *out = live;
       return WF_OK;
     }
@@ -469,7 +658,8 @@ int get_geometry(int nside, int lmax, std::shared_ptr<Geometry>* out) {
   if (g->n_cu <= 0) g->n_cu = 1;
   g->nside = nside;
   g->lmax = lmax;
-  const int rc = build_geometry(*g);
+  int rc = build_geometry(*g);
+  if (!rc && fp64) rc = build_leg64(*g);
   if (rc) return rc;
   g_geo[key] = g;
   *out = g;

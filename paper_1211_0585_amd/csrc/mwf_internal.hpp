@@ -72,15 +72,16 @@ constexpr int CHUNK = 16;            // l-steps per reduction chunk in phase A (
 constexpr int MCH = 32;              // l-steps per staged chunk on the matrix-core path
 constexpr int ROW_PAD = 64;          // zero padding after each per-m row of A / C / coefficients
 constexpr int LANES = 64;            // wavefront width on CDNA
-// FP64 Legendre launches: work items packed at plan time into FP64_WAVES_PER_SIMD
-// bins per SIMD, one wave per bin, by estimated cost in steps of l: a step costs 1,
-// or FP64_SCALED_COST_{ANA,SYN} / 4 while a ring of the item is still scaled (the
-// rescale path runs once per chunk: 16 steps in the analysis, 8 in the synthesis),
-// and an item FP64_ITEM_COST_L more for its set-up. (Weights from timing the kernels.)
-constexpr int FP64_WAVES_PER_SIMD = 3;
+// FP64 Legendre launches: up to FP64_{ANA,SYN}_WAVES waves per CU in one workgroup (as many per
+// SIMD as the registers allow: 168 and 128 a lane). Estimated cost of
+// an item in quarter steps of l: 4 per step, FP64_SCALED_COST_{ANA,SYN} while a ring of the item
+// is still scaled (the rescale path runs once per chunk: 16 steps in the analysis, 8 in the
+// synthesis), and 4 FP64_ITEM_COST_L for its set-up. (Weights from timing the kernels.)
+constexpr int FP64_ANA_WAVES = 12;
+constexpr int FP64_SYN_WAVES = 16;
 constexpr int FP64_SCALED_COST_ANA = 5;
 constexpr int FP64_SCALED_COST_SYN = 6;
-constexpr int FP64_ITEM_COST_L = 32;
+constexpr int FP64_ITEM_COST_L = 16;
 constexpr uint16_t WAKE_NEVER = 0xffff;
 
 // lambda_mm(z) = norm_m sin^m(theta) as v * 2^(-512 s) with |v| >= 2^-449 when s = 0.
@@ -123,10 +124,8 @@ struct PlanDev {
   int32_t nside, lmax, npairs, nrings;
   int64_t npix, nalm;
   double tau, omega;
-  int32_t ring_block_ana;    // ring pairs per Legendre-analysis work item (64 * R)
-  int32_t ring_block_syn;    // ring pairs per Legendre-synthesis work item (64 * R)
-  int32_t nblk_max;          // max analysis blocks per m (partial sums per m)
-  int32_t pad0_;
+  int32_t ring_block_ana;    // ring pairs per FP64 analysis block (64 * R)
+  int32_t nblk_max;          // max FP64 analysis blocks per m (partial sums per m)
   const RingPair* pairs;     // [npairs]
   const void* q;             // [npix] tau * ninv (observed) or 0, in the storage type
   const double* cl;          // [lmax+1]
@@ -149,6 +148,56 @@ struct PlanDev {
   int64_t rows_total;        // length of the padded per-m row layout of A / C / bcoef
   const int32_t* row_m;      // [rows_total] m of each padded row
 };
+
+// Work item of the FP64 Legendre kernels: one m, one block of ring pairs, i0 <= l - m < i1.
+struct Item64 {
+  int32_t m, blk, i0, i1;
+};
+
+// Work list of one FP64 Legendre launch: workgroup b, `waves` waves, shares items[wg[b] ..
+// wg[b + 1]); state and scale hold rb entries per item, the recurrence state
+// (u of odd and even k; the two registers of the equatorial form) of its pairs at i0.
+struct Leg64List {
+  const Item64* items;
+  const int32_t* wg;
+  const double2* state;
+  const uint8_t* scale;
+  int32_t nwg, waves, rb, pad_;
+};
+
+// FP64 Legendre tables of one geometry (see phase_a.hip): recurrence and conversion factors in
+// the padded row layout, and the work lists. Made for the first FP64 plan of a shape.
+struct Leg64Dev {
+  const double* ab[3];     // [rows_total] per form (MID, EQ, CAP): in the slots l - m = 2k and 2k + 1 of the row
+                           // of m, a_k and b_k; -a_k and -(b_k + 2); -a_k and a_k + b_k - 2
+  const double2* co;       // [rows_total] (alpha_i, beta_i): a_lm = alpha_i P_i + beta_i P_{i-2}, i = l - m
+  const double* z;         // [npairs] z of the north ring
+  const int32_t* start;    // [lmax+1][nblk_max] first l - m summed by the analysis in each block
+  Leg64List ana, syn;
+};
+
+// Sum of the analysis blocks' partial sums of one (l, m), i = l - m (FP64), pb at block 0: KB at
+// a time with their loads issued together, blocks that start above i left out (they write
+// nothing there).
+__device__ __forceinline__ double2 block_partials(const PlanDev& P, const Leg64Dev& L, const double2* __restrict__ pb,
+                                                  int m, int i) {
+  constexpr int KB = 4;
+  const int nb = P.nblk[m];
+  const int32_t* __restrict__ i0 = L.start + m * P.nblk_max;
+  double sr = 0.0, si = 0.0;
+  for (int k0 = 0; k0 < nb; k0 += KB) {
+    double2 p[KB];
+#pragma unroll
+    for (int u = 0; u < KB; ++u)
+      p[u] = k0 + u < nb && i >= i0[k0 + u] ? pb[(size_t)(k0 + u) * P.nalm] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < KB; ++u) {
+      sr += p[u].x;
+      si += p[u].y;
+    }
+  }
+  return make_double2(sr, si);
+}
 
 // Elements per ring pair in the G and F buffers ([map][pair][m][E re, E im, O re, O im]):
 // 4 per m <= lmax, unpadded. (Rows padded to whole 128-byte lines made the per-map stride a
@@ -293,16 +342,14 @@ hipError_t launch_phase_b(const PlanDev& P, const PhaseBArgs& a, const RingClass
 hipError_t launch_phase_b_class(const PlanDev& P, const PhaseBArgs& a, const RingClass& rc, int cls, bool fp32,
                                 hipStream_t s);
 
-// Phase A (m-parallel): Legendre analysis into per-block partial sums. One wave per
-// bin: wave w runs items[bins[w] .. bins[w + 1]) (nbins bins).
-hipError_t launch_legendre_analysis_f64(const PlanDev& P, const WorkItem* items, const int32_t* bins,
-                                        int nbins, int nmaps, const double* G, double2* partial,
-                                        hipStream_t s);
+// Phase A (m-parallel): Legendre analysis into per-block partial sums.
+hipError_t launch_legendre_analysis_f64(const PlanDev& P, const Leg64Dev& L, int nmaps, const double* G,
+                                        double2* partial, hipStream_t s);
 
 enum SynthMode : int32_t {
-  SY_FROM_PARTIAL = 0,   // a = C sum(partials); s = f(lambda) a; synthesise s
+  SY_FROM_PARTIAL = 0,   // a from the partial sums; s = f(lambda) a; synthesise s
   SY_FROM_ALM = 1,       // synthesise the caller's alm
-  SY_ALM_ONLY = 2        // a = C sum(partials) -> alm output, no synthesis
+  SY_ALM_ONLY = 2        // a from the partial sums -> alm output, no synthesis
 };
 
 struct SynthArgs {
@@ -312,16 +359,15 @@ struct SynthArgs {
   const double2* partial;   // [map][blk][nalm]
   const double2* alm_in;    // [map][nalm]
   double2* alm_out;         // [map][nalm] or null
-  double2* bcoef;           // [map][rows_total] C_l s_lm in the padded row layout
+  double2* bcoef;           // [map][rows_total] synthesis coefficients in the padded row layout
   double* F;                // [map][pair][m][4]
   double* chi2;             // null, or where map 0 adds sum_lm w_m |s_lm|^2 / C_l (SY_FROM_PARTIAL)
   int64_t chi2_stride;
 };
 
 // Sum of partials, filter and C scaling (one launch over all (l, m, map)).
-hipError_t launch_legendre_coeff(const PlanDev& P, const SynthArgs& a, hipStream_t s);
-hipError_t launch_legendre_synthesis_f64(const PlanDev& P, const WorkItem* items, const int32_t* bins,
-                                         int nbins, const SynthArgs& a, hipStream_t s);
+hipError_t launch_legendre_coeff(const PlanDev& P, const Leg64Dev& L, const SynthArgs& a, hipStream_t s);
+hipError_t launch_legendre_synthesis_f64(const PlanDev& P, const Leg64Dev& L, const SynthArgs& a, hipStream_t s);
 
 // Matrix-core (FP32 / BF16x3) Legendre phase for batches stored in float.
 // Threads per workgroup of the matrix-core coefficient kernel (one element each).
@@ -499,18 +545,24 @@ struct PolCoeffArgs {
   const int32_t* nblk2_m;     // [lmax+1] E/B blocks written for m
   const double2* alm_in;      // [map][3][nalm]
   double2* alm_out;           // [map][3][nalm] or null
-  double2* bcoef_t;           // [map][rows_total]: C_l s_T (spin-0 synthesis input)
+  double2* bcoef_t;           // [map][rows_total]: spin-0 synthesis coefficients of s_T
   double2* bcoef_eb;          // [map][rows_total][2]: -K s_E / 2, -K s_B / 2
   const double* cl4;          // [4][lmax+1] TT, EE, BB, TE
 };
-hipError_t launch_pol_coeff(const PlanDev& P, const Spin2Dev& S2, const PolCoeffArgs& a, hipStream_t s);
+hipError_t launch_pol_coeff(const PlanDev& P, const Leg64Dev& L, const Spin2Dev& S2, const PolCoeffArgs& a,
+                            hipStream_t s);
 hipError_t launch_spin2_analysis(const PlanDev& P, const Spin2Dev& S2, int nmaps, const double* G, double* partial_eb,
                                  int nblk2, hipStream_t s);
 hipError_t launch_spin2_synthesis(const PlanDev& P, const Spin2Dev& S2, int nmaps, const double2* bcoef_eb, double* F,
                                   hipStream_t s);
 
-// Plan-time, per (m, ring pair): where lambda_lm leaves the scaled range, or WAKE_NEVER
-// (polar skip and the cost of the FP64 work items).
-hipError_t launch_reach(const PlanDev& P, uint16_t* wake, hipStream_t s);
+// Plan-time, per (m, ring pair): where lambda_lm leaves the scaled range and where it exceeds
+// 2^-128, or WAKE_NEVER (polar skip, start and cost of the FP64 work items).
+hipError_t launch_reach(const PlanDev& P, uint16_t* wake, uint16_t* rise, hipStream_t s);
+// Plan-time: state and scale of a work list, from its items and the tables of L.
+hipError_t launch_start_state(const PlanDev& P, const Leg64Dev& L, const Leg64List& T, int nitems, int ch,
+                              double2* state, uint8_t* scale, hipStream_t s);
+// Raise the dynamic-LDS limit of `kernel` on the current device to at least `lds` (never lower it).
+hipError_t ensure_dynamic_lds(const void* kernel, size_t lds);
 
 }  // namespace mwf

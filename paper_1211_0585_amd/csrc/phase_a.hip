@@ -11,12 +11,29 @@
 //
 // using lambda_lm(-z) = (-1)^(l+m) lambda_lm(z) for the mirror rings.
 //
-// The recurrence runs on rescaled values mu_l = lambda_lm / C_lm that obey
-//   mu_l = (A_lm z) mu_{l-1} - mu_{l-2}
-// (A and C are plan-time FP64 tables derived from
-//  a_lm = sqrt((4 l^2 - 1)/(l^2 - m^2)) with C_l = C_{l-2} a_l / a_{l-1}, A_l = a_l C_{l-1} / C_l),
-// i.e. one multiply and one FMA per value; C is applied once per (l, m) after the
-// ring sum (analysis) or folded into s_lm (synthesis).
+// Two values of l per recurrence step (Ishioka 2018, J. Meteorol. Soc. Japan 96, 241). With
+// eps_l = sqrt((l^2 - m^2) / (4 l^2 - 1)), z lambda_l = eps_{l+1} lambda_{l+1} + eps_l lambda_{l-1},
+// and the even polynomials p_k = lambda_{m+2k+1} / z one has
+//   lambda_{m+2k+1} = z p_k,   lambda_{m+2k} = eps_{m+2k+1} p_k + eps_{m+2k} p_{k-1},
+//   eps_{l+1} eps_{l+2} p_{k+1} = (z^2 - eps_{l+1}^2 - eps_l^2) p_k - eps_l eps_{l-1} p_{k-1}
+// (l = m + 2k + 1). Rescaled, p_k = c_k u_k, this is u_k = (a_k z^2 + b_k) u_{k-1} - u_{k-2}:
+// two FMAs for the pair (l, l + 1), where the step in l took a multiply and an FMA for each.
+// The ring sums then run on u_k alone, S_k = sum u_k S and T_k = sum u_k (z D), and the
+// coefficient kernel turns them into alm (and alm into the synthesis coefficients) with two
+// factors per l:  a_{m+2k} = eps_{m+2k+1} c_k S_k + eps_{m+2k} c_{k-1} S_{k-1}, a_{m+2k+1} = c_k T_k.
+// FP64 operations per (l, m, ring pair): 1 in the recurrence and 2 in the sums, against 2 and 2.
+// FP64 issue bounds both kernels (the FP64 matrix instructions share the same units: a probe
+// with both in flight took the sum of their times), so the operations left out are the gain.
+//
+// Near the equator a z^2 + b comes close to -2 and towards the poles to +2, where rounding
+// grows along the recurrence like 1 / sin(2 theta). The first 256 ring pairs therefore carry
+// v_k = u_k + u_{k-1}, with alternating signs folded in (ut_k = (-1)^k u_k, vt likewise), and
+// the blocks of the polar caps the differences v_k = u_k - u_{k-1}:
+//   equator  vt_{k+1} = vt_k - (a_k z^2 + b_k + 2) ut_k,              ut_{k+1} = ut_k + vt_{k+1}
+//   caps     v_{k+1} = v_k + (a_k + b_k - 2 - a_k sin^2 theta) u_k,    u_{k+1} = u_k + v_{k+1}
+// (two FMAs and an add for the step). Error of the transform pair at Nside 1024 against 64-bit
+// sums: 2.1e-14; 5.3e-14 with the plain form everywhere, 1.5e-14 with the step in l. (Nside 512, eight
+// sweeps: 0.9e-14 against 1.1e-14.)
 //
 // The sectoral seed lambda_mm = norm_m sin^m(theta) underflows FP64 near the
 // poles: every value carries an integer scale s (value = v 2^(-512 s)). The scale
@@ -24,14 +41,33 @@
 // a ring whose scale is still positive at the start of a chunk contributes
 // nothing in that chunk (its values are below 2^-448 times the growth of one
 // chunk, far under FP64 resolution of the sums). The recurrence alternates
-// between two registers, so a step is one multiply and one FMA and no moves.
+// between two registers, so a step has no moves.
 //
-// Each work item is (m, block of 64 R ring pairs) handled by one wavefront; a
-// lane owns R ring pairs. The recurrence coefficients (and, in the synthesis, the
-// filtered a_lm) are fetched 64 values of l ahead with one vector load and read
-// from LDS. The analysis reduces over lanes through LDS once per chunk of 16
-// values of l and writes one partial sum per block; a small kernel sums the
-// partials of each (l, m), applies the filter and scales by C for the synthesis.
+// Work items are (m, block of 64 R ring pairs, range of l), one wavefront each; a lane owns R
+// ring pairs. An item starts from a recurrence state made at plan time, so its seeds cost a
+// load, it can start anywhere in l, and the l at which every ring of the block is still below
+// 2^-128 (m well above l sin(theta)) are not generated, summed or written at all (12 to 20 %
+// of the steps). The analysis splits a block's l into several items, since their outputs are
+// independent: with one item per (m, block) at Nside 512, 3500 items for 3072 waves, the
+// longest set the launch's time (1.67 of the mean). The synthesis sums over l and takes smaller
+// blocks instead where there are few items.
+//
+// A launch is one workgroup per CU of up to 12 (analysis) or 16 waves. The items are balanced over
+// the workgroups at plan time; inside one the waves take them from a shared queue.
+//
+// The recurrence coefficients are fetched 64 values of l ahead with one vector load and read
+// from LDS; the synthesis coefficients, twice as many, are held 16 to a row of lanes and
+// broadcast by the FMAs themselves (see accumulate). The analysis reduces over lanes through
+// LDS once per chunk of 16 values of l and writes one partial sum per block; a small kernel sums
+// the partials of each (l, m), applies the filter and forms the synthesis coefficients.
+//
+// One map, Nside 512, lmax 1024: analysis 136 -> 104 us, synthesis 102 -> 75 us; Nside 1024,
+// lmax 2048: 977 -> 672 and 748 -> 466 us; Nside 64, lmax 191: synthesis 10.9 -> 6.9 us. At
+// Nside 1024 the synthesis issues FP64 at four fifths of the rate a chain of independent FMAs
+// reaches with as many waves; the analysis loses another tenth to its reductions, and at Nside
+// 512 an item's set-up (ring states and S/D, 256 rows of G apart) weighs more.
+#include <type_traits>
+
 #include "mwf_internal.hpp"
 
 namespace mwf {
@@ -39,6 +75,7 @@ namespace {
 
 constexpr double BIG_THRESH = 0x1p64;
 constexpr double RESCALE = 0x1p-512;
+constexpr double RISE_THRESH = 0x1p-128;   // values below this are left out of the FP64 sums' work
 
 __device__ __forceinline__ int wave_any(int pred) { return __any(pred); }
 
@@ -52,33 +89,54 @@ __device__ __forceinline__ double fold_halves(double a, double b) {
   return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
 }
 
+// Forms of the recurrence (see above) and the form of a block of rb ring pairs.
+enum Form { MID = 0, EQ = 1, CAP = 2 };
+__device__ __forceinline__ int block_form(const PlanDev& P, int blk, int rb) {
+  return (blk + 1) * rb <= 256 ? EQ : (blk * rb >= P.nside ? CAP : MID);
+}
+
+// Recurrence state of a lane's ring pairs: z^2 (sin^2 theta in the CAP form), the two registers
+// (u of the latest odd and even k, or u and v), and the scales.
 template <int R>
 struct RingState {
-  double z[R], mu1[R], mu2[R];
-  int sc[R];
+  double zz[R], u1[R], u2[R];
+  unsigned sc;   // a byte per ring pair (at most four)
 };
 
-template <int R>
-__device__ __forceinline__ void init_rings(const PlanDev& P, int m, int blk, int lane, int nact,
-                                           RingState<R>& st) {
+// The plan's start state of item k (zero past the active ring pairs).
+template <int R, int FORM>
+__device__ __forceinline__ void init_rings(const PlanDev& P, const Leg64List& T, const double* __restrict__ zt, int k,
+                                           int blk, int lane, int nact, RingState<R>& st, double (&z)[R]) {
+  st.sc = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int q = blk * (LANES * R) + r * LANES + lane;
-    if (q < nact) {
-      const RingPair rp = P.pairs[q];
-      double v;
-      int s;
-      sectoral_seed(m, rp.sin_t, P.norm_m[m], &v, &s);
-      st.z[r] = rp.z;
-      st.mu1[r] = 0.0;    // mu_{m-1}
-      st.mu2[r] = -v;     // with A_mm = 0 the first step yields mu_m = v
-      st.sc[r] = s;
-    } else {
-      st.z[r] = 0.0;
-      st.mu1[r] = 0.0;
-      st.mu2[r] = 0.0;
-      st.sc[r] = 0;
-    }
+    const size_t at = (size_t)k * (LANES * R) + r * LANES + lane;
+    const double2 u = T.state[at];
+    z[r] = q < nact ? zt[min(q, P.npairs - 1)] : 0.0;
+    st.zz[r] = FORM == CAP ? (1.0 - z[r]) * (1.0 + z[r]) : z[r] * z[r];
+    st.u1[r] = u.x;
+    st.u2[r] = u.y;
+    st.sc |= (unsigned)T.scale[at] << (8 * r);
+  }
+}
+
+// One step pair (k even, then odd) of a ring: use(0, u_k) and use(1, u_{k+1}, or -u_{k+1} in the
+// EQ form); c0 and c1 the coefficients of the two steps in the table of the form.
+template <int FORM, class Use>
+__device__ __forceinline__ void step_pair(double& u1, double& u2, double zz, double2 c0, double2 c1, Use use) {
+  if constexpr (FORM != MID) {
+    u2 = fma(fma(c0.x, zz, c0.y), u1, u2);   // u2 = v, u1 = u
+    u1 = u1 + u2;
+    use(0, u1);
+    u2 = fma(fma(c1.x, zz, c1.y), u1, u2);
+    u1 = u1 + u2;
+    use(1, u1);                              // (EQ: -u_k)
+  } else {
+    u2 = fma(fma(c0.x, zz, c0.y), u1, -u2);
+    use(0, u2);
+    u1 = fma(fma(c1.x, zz, c1.y), u2, -u1);
+    use(1, u1);
   }
 }
 
@@ -89,11 +147,11 @@ __device__ __forceinline__ int rescale_chunk(RingState<R>& st) {
   int woke = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    if (st.sc[r] > 0 && fmax(fabs(st.mu1[r]), fabs(st.mu2[r])) > BIG_THRESH) {
-      st.mu1[r] *= RESCALE;
-      st.mu2[r] *= RESCALE;
-      st.sc[r] -= 1;
-      if (st.sc[r] == 0) woke |= 1 << r;
+    if (((st.sc >> (8 * r)) & 0xff) != 0 && fmax(fabs(st.u1[r]), fabs(st.u2[r])) > BIG_THRESH) {
+      st.u1[r] *= RESCALE;
+      st.u2[r] *= RESCALE;
+      st.sc -= 1u << (8 * r);
+      if (((st.sc >> (8 * r)) & 0xff) == 0) woke |= 1 << r;
     }
   }
   return woke;
@@ -101,318 +159,400 @@ __device__ __forceinline__ int rescale_chunk(RingState<R>& st) {
 
 constexpr int LTILE = 64;  // values of l per prefetched coefficient tile (one per lane)
 
-// FP64 Legendre launches: workgroups of FP64_WG_WAVES waves, one bin each, so that
-// every SIMD of a CU gets the same number of waves (with single-wave workgroups
-// the spread over a CU's SIMDs depends on what ran before: after a ring phase of
-// three concurrent launches, some SIMDs got four waves and some two, and the
-// launch took a third longer).
-constexpr int FP64_WG_WAVES = 4;
-
 // Orders a wave's LDS accesses around it (one wave's LDS operations execute in
 // order; this keeps the compiler from moving them across).
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 constexpr int ACH = 16;    // analysis: values of l per cross-lane reduction (and scale check)
 static_assert(LTILE % ACH == 0 && (2 * ACH) <= LANES, "analysis chunking");
 
-template <int R>
-__global__ void __launch_bounds__(FP64_WG_WAVES * LANES) legendre_analysis_f64_kernel(
-    PlanDev P, const WorkItem* __restrict__ items, const int32_t* __restrict__ bins, int nbins,
-    const double* __restrict__ G, double2* __restrict__ partial) {
-  // per-wave LDS: the waves of a workgroup run unrelated bins and never synchronise
-  __shared__ double red_w[FP64_WG_WAVES][2 * ACH][LANES / 2 + 1];
-  __shared__ double sA_w[FP64_WG_WAVES][LTILE];
-  const int wave = threadIdx.x / LANES;
-  const int bin = blockIdx.x * FP64_WG_WAVES + wave;
-  if (bin >= nbins) return;
-  double(*red)[LANES / 2 + 1] = red_w[wave];
-  double* sA = sA_w[wave];
-  const int map = blockIdx.y;
-  // this wave's bin of work items (packed at plan time)
-  const int k_end = bins[bin + 1];
-  for (int k = bins[bin]; k < k_end; ++k) {
-    const WorkItem it = items[k];
-    const int m = it.m, blk = it.blk;
-    const int lane = threadIdx.x % LANES;
-    const int lmax = P.lmax;
-    const int nact = P.n_active[m];
-    const double* __restrict__ Arow = P.A + P.row_off[m];
-    const size_t pstride = gf_stride(lmax);
-    const double* Gm = G + (size_t)map * P.npairs * pstride + (size_t)m * 4;
+// LDS of one wave: the cross-lane reduction (values x 32 lanes, padded) and the coefficient tile.
+constexpr int RED_STRIDE = LANES / 2 + 1;
+constexpr int ANA_LDS = 2 * ACH * RED_STRIDE + LTILE;   // doubles per wave
 
-    RingState<R> st;
-    init_rings<R>(P, m, blk, lane, nact, st);
-    // S/D of each ring, zero while the ring's values are still scaled
-    double Sre[R], Sim[R], Dre[R], Dim[R];
+// The items of this workgroup, taken by its waves one at a time, most costly first, through a
+// counter in LDS. A SIMD issues from its oldest ready wave, so with the items dealt to the
+// waves beforehand the first wave of each SIMD finished at 0.59 of the launch, the second at
+// 0.79, and the last ran its rest alone, with nothing to hide its latencies.
+struct ItemQueue {
+  int* ctr;
+  int first, end, k = 0;
+  __device__ __forceinline__ ItemQueue(const Leg64List& T, double* lds)
+      : ctr(reinterpret_cast<int*>(lds)), first(T.wg[blockIdx.x]), end(T.wg[blockIdx.x + 1]) {
+    if (threadIdx.x == 0) *ctr = first;
+    __syncthreads();
+  }
+  __device__ __forceinline__ bool next(int lane) {
+    int v = 0;
+    if (lane == 0) v = atomicAdd(ctr, 1);
+    k = __builtin_amdgcn_readfirstlane(v);
+    return k < end;
+  }
+};
+
+template <int R, int FORM>
+__device__ __forceinline__ void analysis_item(const PlanDev& P, const Leg64Dev& L, const int k, const Item64 it,
+                                              const int map, const int lane, double* __restrict__ lds,
+                                              const double* __restrict__ G, double2* __restrict__ partial) {
+  double* red = lds;
+  double* sA = lds + 2 * ACH * RED_STRIDE;
+  const int m = it.m, blk = it.blk;
+  const int nact = P.n_active[m];
+  const double* __restrict__ Arow = L.ab[FORM] + P.row_off[m] + it.i0;
+  const size_t pstride = gf_stride(P.lmax);
+  const double* Gm = G + (size_t)map * P.npairs * pstride + (size_t)m * 4;
+
+  RingState<R> st;
+  double z[R];
+  init_rings<R, FORM>(P, L.ana, L.z, k, blk, lane, nact, st, z);
+  // S and z D of each ring, zero while the ring's values are still scaled
+  double Sre[R], Sim[R], Dre[R], Dim[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int q = blk * (LANES * R) + r * LANES + lane;
-      if (q < nact && st.sc[r] == 0) {
-        const double4 sd = *reinterpret_cast<const double4*>(Gm + (size_t)q * pstride);
-        Sre[r] = sd.x;
-        Sim[r] = sd.y;
-        Dre[r] = sd.z;
-        Dim[r] = sd.w;
-      } else {
-        Sre[r] = Sim[r] = Dre[r] = Dim[r] = 0.0;
-      }
+  for (int r = 0; r < R; ++r) {
+    const int q = blk * (LANES * R) + r * LANES + lane;
+    // (loaded whatever the scale, so that the load does not wait for the state)
+    const double4 sd = *reinterpret_cast<const double4*>(Gm + (size_t)min(q, nact - 1) * pstride);
+    const bool on = q < nact && ((st.sc >> (8 * r)) & 0xff) == 0;
+    Sre[r] = on ? sd.x : 0.0;
+    Sim[r] = on ? sd.y : 0.0;
+    Dre[r] = on ? z[r] * sd.z : 0.0;
+    Dim[r] = on ? z[r] * sd.w : 0.0;
+  }
+
+  // the item's part of the block's partial sums
+  const int nl = it.i1 - it.i0;
+  double* out = reinterpret_cast<double*>(partial + ((size_t)map * P.nblk_max + blk) * P.nalm +
+                                          alm_index(P.lmax, m, m) + it.i0);
+
+  // recurrence coefficients of LTILE values of l (the two factors of step k in the slots of
+  // l - m = 2k and 2k + 1): lane i loads slot base + i one tile ahead, the tile in use is read
+  // from LDS (the same address in every lane). The loads are unconditional, with the index
+  // clamped to the row's end (past it all slots are zero), so that no wait for them lands
+  // inside the loop.
+  const int na = P.lmax - m + 2 - it.i0;
+  auto tile_a = [&](int i) { return Arow[min(i, na)]; };
+  sA[lane] = tile_a(lane);
+  // every load issued so far (ring states, S/D, tile 0) completes here, so the loop
+  // body waits on nothing but its own LDS reads
+  __builtin_amdgcn_s_waitcnt(0);
+  wave_sync();
+  double An = tile_a(LTILE + lane);
+
+  for (int i = 0; i < nl; i += ACH) {
+    const int t0 = i & (LTILE - 1);
+    if (t0 == 0 && i > 0) {
+      sA[lane] = An;      // the previous tile's last readers passed the barrier below
+      wave_sync();
+      An = tile_a(i + LTILE + lane);
     }
-
-    double* out = reinterpret_cast<double*>(partial + ((size_t)map * P.nblk_max + blk) * P.nalm);
-    const int64_t row = alm_index(lmax, m, m);
-
-    // recurrence coefficients of LTILE values of l: lane i loads l = base + i one
-    // tile ahead, the tile in use is read from LDS (the same address in every lane).
-    // The loads are unconditional, with the index clamped to nl (the first entry of
-    // the row's zero padding), so that no wait for them lands inside the loop.
-    const int nl = lmax - m + 1;
-    auto tile_a = [&](int i) { return Arow[min(i, nl)]; };
-    sA[lane] = tile_a(lane);
-    // every load issued so far (ring seeds, S/D, tile 0) completes here, so the loop
-    // body waits on nothing but its own LDS reads
-    __builtin_amdgcn_s_waitcnt(0);
+    double are[ACH], aim[ACH];
+#pragma unroll
+    for (int j = 0; j < ACH; ++j) are[j] = aim[j] = 0.0;
+    const double2* Ac = reinterpret_cast<const double2*>(sA + t0);
+#pragma unroll
+    for (int j = 0; j < ACH; j += 4) {
+      const double2 c0 = Ac[j / 2], c1 = Ac[j / 2 + 1];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        step_pair<FORM>(st.u1[r], st.u2[r], st.zz[r], c0, c1, [&](int h, double x) {
+          const int v = j + 2 * h;
+          const double u = FORM == EQ && h == 1 ? -x : x;
+          are[v] = fma(u, Sre[r], are[v]);
+          aim[v] = fma(u, Sim[r], aim[v]);
+          are[v + 1] = fma(u, Dre[r], are[v + 1]);
+          aim[v + 1] = fma(u, Dim[r], aim[v + 1]);
+        });
+      // keeps the tile reads of all the steps from moving up here, where they cost the
+      // registers that let a third wave in
+      if (j == ACH / 2) __builtin_amdgcn_sched_barrier(0);
+    }
+    // reduce the NV = 2 ACH values (v = 2 j + re/im) over the 64 lanes: first lanes
+    // l and l + 32 in registers, the lower half keeping values 0..NV/2-1 and the
+    // upper half the rest, then the remaining 32 lanes through LDS, LPV lanes per
+    // value each adding 32 / LPV entries, and LPV - 1 shuffles
+    constexpr int NV = 2 * ACH, LPV = LANES / NV;
+#pragma unroll
+    for (int x = 0; x < ACH; ++x) {
+      const int ja = x >> 1, jb = ACH / 2 + (x >> 1);
+      const double va = (x & 1) ? aim[ja] : are[ja];
+      const double vb = (x & 1) ? aim[jb] : are[jb];
+      red[(x + (lane >> 5) * ACH) * RED_STRIDE + (lane & 31)] = fold_halves(va, vb);
+    }
     wave_sync();
-    double An = tile_a(LTILE + lane);
-
-    for (int l0 = m; l0 <= lmax; l0 += ACH) {
-      const int t0 = (l0 - m) & (LTILE - 1);
-      if (t0 == 0 && l0 > m) {
-        sA[lane] = An;      // the previous tile's last readers passed the barrier below
-        wave_sync();
-        An = tile_a(l0 - m + LTILE + lane);
-      }
-      double are[ACH], aim[ACH];
+    const int v = lane / LPV;
+    const double* rv = red + v * RED_STRIDE + (lane % LPV) * (32 / LPV);
+    double part[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int j = 0; j < ACH; ++j) are[j] = aim[j] = 0.0;
-      const double* Ac = sA + t0;
+    for (int x = 0; x < 32 / LPV; ++x) part[x & 3] += rv[x];
+    double sum = (part[0] + part[1]) + (part[2] + part[3]);
 #pragma unroll
-      for (int j = 0; j < ACH; j += 2) {
-        const double A0 = Ac[j], A1 = Ac[j + 1];
+    for (int x = 1; x < LPV; x <<= 1) sum += __shfl_xor(sum, x);
+    if (lane % LPV == 0 && i + (v >> 1) < nl) out[2 * (i + (v >> 1)) + (v & 1)] = sum;
+    wave_sync();
+    const int woke = wave_any(st.sc != 0) ? rescale_chunk<R>(st) : 0;
+    if (woke) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          // mu2 <- mu_l (l - m even), then mu1 <- mu_{l+1} (odd)
-          st.mu2[r] = fma(A0 * st.z[r], st.mu1[r], -st.mu2[r]);
-          are[j] = fma(st.mu2[r], Sre[r], are[j]);
-          aim[j] = fma(st.mu2[r], Sim[r], aim[j]);
-          st.mu1[r] = fma(A1 * st.z[r], st.mu2[r], -st.mu1[r]);
-          are[j + 1] = fma(st.mu1[r], Dre[r], are[j + 1]);
-          aim[j + 1] = fma(st.mu1[r], Dim[r], aim[j + 1]);
+      for (int r = 0; r < R; ++r)
+        if (woke & (1 << r)) {
+          const int q = blk * (LANES * R) + r * LANES + lane;
+          const double4 sd = *reinterpret_cast<const double4*>(Gm + (size_t)q * pstride);
+          const double zq = L.z[q];
+          Sre[r] = sd.x;
+          Sim[r] = sd.y;
+          Dre[r] = zq * sd.z;
+          Dim[r] = zq * sd.w;
         }
-      }
-      // reduce the NV = 2 ACH values (v = 2 j + re/im) over the 64 lanes: first lanes
-      // l and l + 32 in registers, the lower half keeping values 0..NV/2-1 and the
-      // upper half the rest, then the remaining 32 lanes through LDS, LPV lanes per
-      // value each adding 32 / LPV entries, and LPV - 1 shuffles
-      constexpr int NV = 2 * ACH, LPV = LANES / NV;
-#pragma unroll
-      for (int i = 0; i < ACH; ++i) {
-        const int ja = i >> 1, jb = ACH / 2 + (i >> 1);
-        const double va = (i & 1) ? aim[ja] : are[ja];
-        const double vb = (i & 1) ? aim[jb] : are[jb];
-        red[i + (lane >> 5) * ACH][lane & 31] = fold_halves(va, vb);
-      }
-      wave_sync();
-      const int v = lane / LPV;
-      const int h = (lane % LPV) * (32 / LPV);
-      double sum = 0.0;
-#pragma unroll
-      for (int k = 0; k < 32 / LPV; ++k) sum += red[v][h + k];
-#pragma unroll
-      for (int x = 1; x < LPV; x <<= 1) sum += __shfl_xor(sum, x);
-      if (lane % LPV == 0) {
-        const int l = l0 + (v >> 1);
-        if (l <= lmax) out[2 * (row + (l - m)) + (v & 1)] = sum;
-      }
-      wave_sync();
-      int anysc = 0;
-#pragma unroll
-      for (int r = 0; r < R; ++r) anysc |= st.sc[r];
-      const int woke = wave_any(anysc) ? rescale_chunk<R>(st) : 0;
-      if (woke) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-          if (woke & (1 << r)) {
-            const int q = blk * (LANES * R) + r * LANES + lane;
-            const double4 sd = *reinterpret_cast<const double4*>(Gm + (size_t)q * pstride);
-            Sre[r] = sd.x;
-            Sim[r] = sd.y;
-            Dre[r] = sd.z;
-            Dim[r] = sd.w;
-          }
-        // (rare) complete these loads here rather than at their first use, where the
-        // wait would also cover the tile prefetch
-        __builtin_amdgcn_s_waitcnt(0);
-      }
+      // (rare) complete these loads here rather than at their first use, where the
+      // wait would also cover the tile prefetch
+      __builtin_amdgcn_s_waitcnt(0);
+    }
+  }
+  wave_sync();   // the next item's tile 0 is written after this one's last reads
+}
+
+template <int R>
+__global__ void __launch_bounds__(FP64_ANA_WAVES * LANES) legendre_analysis_f64_kernel(PlanDev P, Leg64Dev L,
+                                                                     const double* __restrict__ G,
+                                                                     double2* __restrict__ partial) {
+  // the queue's counter, then per-wave LDS: waves run unrelated items and never synchronise
+  extern __shared__ __attribute__((aligned(16))) double leg64_lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
+  const int lane = threadIdx.x % LANES;
+  double* lds = leg64_lds + 2 + wave * ANA_LDS;
+  for (ItemQueue q(L.ana, leg64_lds); q.next(lane);) {
+    const int k = q.k;
+    const Item64 it = L.ana.items[k];
+    switch (block_form(P, it.blk, LANES * R)) {
+      case EQ: analysis_item<R, EQ>(P, L, k, it, blockIdx.y, lane, lds, G, partial); break;
+      case CAP: analysis_item<R, CAP>(P, L, k, it, blockIdx.y, lane, lds, G, partial); break;
+      default: analysis_item<R, MID>(P, L, k, it, blockIdx.y, lane, lds, G, partial);
     }
   }
 }
 
-// Filtered coefficients for the synthesis, one thread per (l, m, map):
-//   SY_FROM_PARTIAL  a = C_l sum_blk partial, s = f_l(lambda) a
-//   SY_ALM_ONLY      a = C_l sum_blk partial (the forward transform), s = a
+// Filtered coefficients for the synthesis, one thread per (l, m, map), from the sums
+// P_i of the blocks (i = l - m; S_k at i = 2k, T_k at i = 2k + 1) and the plan's factors:
+//   SY_FROM_PARTIAL  a_i = alpha_i P_i + beta_i P_{i-2}, s = f_l(lambda) a
+//   SY_ALM_ONLY      the same a (the forward transform), s = a
 //   SY_FROM_ALM      s = caller's alm (imaginary part of m = 0 dropped)
-// s goes to alm_out when requested; bcoef = C_l s, in the padded row layout of
-// the recurrence tables (zeros beyond lmax) so the synthesis can read whole chunks.
+// s goes to alm_out when requested; bcoef_i = alpha_i s_i + beta_{i+2} s_{i+2} (the transpose;
+// beta is zero at odd i and in the padding), in the padded row layout of the recurrence
+// tables (zeros beyond lmax) so the synthesis can read whole chunks.
 // A flat grid over the padded rows r of every m (m = row_m[r], l = m + r - row_off[m];
 // padding rows get zeros) and the maps: with one workgroup per m instead, the long rows
-// of small m went to a few waves in turn, each waiting on its loads.
-__global__ void legendre_coeff_kernel(PlanDev P, SynthArgs a) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// of small m went to a few waves in turn, each waiting on its loads. A workgroup writes
+// COEFF_ROWS rows and forms P and s for two more on either side, the neighbours its own need
+// (exchanged through LDS; 1.6 % more reads than rows).
+constexpr int COEFF_WG = 256, COEFF_ROWS = COEFF_WG - 4;
+
+__global__ void __launch_bounds__(COEFF_WG) legendre_coeff_kernel(PlanDev P, Leg64Dev L, SynthArgs a) {
+  __shared__ double2 sP[COEFF_WG], sS[COEFF_WG];
+  const int t = threadIdx.x;
+  const int64_t r = (int64_t)blockIdx.x * COEFF_ROWS + t - 2;
   const int map = blockIdx.y;
+  const bool own = t >= 2 && t < 2 + COEFF_ROWS && r < P.rows_total;
   const bool chi = a.chi2 != nullptr && a.mode == SY_FROM_PARTIAL;
   double chi_acc = 0.0;
-  if (r < P.rows_total) {
-    const int lmax = P.lmax;
-    const int m = P.row_m[r];
-    const int i = (int)(r - P.row_off[m]);
-    const int nl = lmax - m + 1;
-    double2 b = make_double2(0.0, 0.0);
-    if (i < nl) {
-      const int64_t row = alm_index(lmax, m, m);
-      const double c = P.C[r];
-      double2 alm;
-      if (a.mode == SY_FROM_ALM) {
-        alm = a.alm_in[(size_t)map * P.nalm + row + i];
-        if (m == 0) alm.y = 0.0;
-      } else {
-        // the blocks' partial sums, KB at a time with their loads issued together
-        constexpr int KB = 4;
-        const int nb = P.nblk[m];
-        const double2* pb = a.partial + (size_t)map * P.nblk_max * P.nalm + row + i;
-        double sr = 0.0, si = 0.0;
-        for (int k0 = 0; k0 < nb; k0 += KB) {
-          double2 p[KB];
-#pragma unroll
-          for (int u = 0; u < KB; ++u) p[u] = k0 + u < nb ? pb[(size_t)(k0 + u) * P.nalm] : make_double2(0.0, 0.0);
-#pragma unroll
-          for (int u = 0; u < KB; ++u) {
-            sr += p[u].x;
-            si += p[u].y;
-          }
-        }
-        // the ring phase already applied Omega to G
-        alm = make_double2(sr * c, si * c);
-        if (a.mode == SY_FROM_PARTIAL) {
-          const double cl = P.cl[m + i];
-          const double f = cl > 0.0 ? cl / (cl + a.lambda * P.tau * P.omega) : 0.0;
-          alm.x *= f;
-          alm.y *= f;
-          // chi^2 prior term of the new iterate: w_m |s_lm|^2 / C_l (w = 1 at m = 0, else 2)
-          if (chi && cl > 0.0) chi_acc = (m == 0 ? 1.0 : 2.0) * (alm.x * alm.x + alm.y * alm.y) / cl;
-        }
-      }
-      if (a.alm_out) a.alm_out[(size_t)map * P.nalm + row + i] = alm;
-      b = make_double2(alm.x * c, alm.y * c);
+  const int lmax = P.lmax;
+  int m = 0, i = 0;
+  bool val = false;
+  double2 co = make_double2(0.0, 0.0);
+  if (r >= 0 && r < P.rows_total) {
+    m = P.row_m[r];
+    i = (int)(r - P.row_off[m]);
+    val = i < lmax - m + 1;
+    if (val) co = L.co[r];
+  }
+  const int64_t at = alm_index(lmax, m, m) + i;
+  double2 p = make_double2(0.0, 0.0), s = p;
+  if (a.mode == SY_FROM_ALM) {
+    if (val) {
+      s = a.alm_in[(size_t)map * P.nalm + at];
+      if (m == 0) s.y = 0.0;
     }
-    if (a.mode != SY_ALM_ONLY) a.bcoef[(size_t)map * P.rows_total + r] = b;
+  } else {
+    if (val) p = block_partials(P, L, a.partial + (size_t)map * P.nblk_max * P.nalm + at, m, i);
+    sP[t] = p;
+    __syncthreads();
+    if (val && t >= 2) {
+      // the ring phase already applied Omega to G
+      s = make_double2(co.x * p.x, co.x * p.y);
+      if (co.y != 0.0) {
+        const double2 q = sP[t - 2];
+        s.x = fma(co.y, q.x, s.x);
+        s.y = fma(co.y, q.y, s.y);
+      }
+      if (a.mode == SY_FROM_PARTIAL) {
+        const double cl = P.cl[m + i];
+        const double f = cl > 0.0 ? cl / (cl + a.lambda * P.tau * P.omega) : 0.0;
+        s.x *= f;
+        s.y *= f;
+        // chi^2 prior term of the new iterate: w_m |s_lm|^2 / C_l (w = 1 at m = 0, else 2)
+        if (chi && own && cl > 0.0) chi_acc = (m == 0 ? 1.0 : 2.0) * (s.x * s.x + s.y * s.y) / cl;
+      }
+    }
+  }
+  if (own && val && a.alm_out) a.alm_out[(size_t)map * P.nalm + at] = s;
+  if (a.mode != SY_ALM_ONLY) {
+    sS[t] = s;
+    __syncthreads();
+    if (own) {
+      double2 b = make_double2(co.x * s.x, co.x * s.y);
+      const double beta = val ? L.co[r + 2].y : 0.0;   // (a row ends in padding: r + 2 stays inside it)
+      if (beta != 0.0) {
+        const double2 n = sS[t + 2];
+        b.x = fma(beta, n.x, b.x);
+        b.y = fma(beta, n.y, b.y);
+      }
+      a.bcoef[(size_t)map * P.rows_total + r] = b;
+    }
   }
   if (chi) block_sum_add(chi_acc, a.chi2 + map * a.chi2_stride);
 }
 
-constexpr int SCH = 8;   // synthesis steps per coefficient chunk
+constexpr int SCH = 16;   // synthesis: values of l per coefficient tile and scale check
+static_assert(LTILE % SCH == 0 && SCH == CHUNK, "synthesis chunking");
+
+// e_r += +-u_r b_V and o_r += +-u_r b_{V+1} (complex b) for the R ring pairs of a lane. Lane i of
+// every row of 16 holds b_i of a tile of 16; the FMAs take the lane of the row they need as an
+// operand (DPP row_newbcast), so the coefficients cost neither LDS nor registers: read from LDS
+// as broadcasts they took as long as the FP64 work (32 bytes per lane and FMA quartet, and one
+// LDS for four SIMDs), through the scalar cache every chunk waited on it. The s_nop covers a
+// write of bx or by just before (two wait states before a DPP read).
+#define MWF_FMAC(ACC, B, SGN, U, LANE) \
+  "\n\tv_fmac_f64_dpp %" ACC ", %" B ", " SGN "%" U " row_newbcast:%" LANE " row_mask:0xf bank_mask:0xf"
+#define MWF_RING(A0, A1, A2, A3, SGN, U) \
+  MWF_FMAC(A0, "[x]", SGN, U, "[v]")     \
+  MWF_FMAC(A1, "[y]", SGN, U, "[v]") MWF_FMAC(A2, "[x]", SGN, U, "[w]") MWF_FMAC(A3, "[y]", SGN, U, "[w]")
+#define MWF_OUT(r) "+v"(er[r]), "+v"(ei[r]), "+v"(orr[r]), "+v"(oi[r])
+#define MWF_IN [x] "v"(bx), [y] "v"(by), [v] "n"(V), [w] "n"(V + 1)
+#define MWF_ACCUMULATE(SGN)                                                                                       \
+  if constexpr (R == 1)                                                                                           \
+    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", SGN, "[p]") : MWF_OUT(0) : MWF_IN, [p] "v"(u[0]));         \
+  else if constexpr (R == 2)                                                                                      \
+    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", SGN, "[p]") MWF_RING("4", "5", "6", "7", SGN, "[q]")       \
+                 : MWF_OUT(0), MWF_OUT(1) : MWF_IN, [p] "v"(u[0]), [q] "v"(u[1]));                                 \
+  else                                                                                                            \
+    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", SGN, "[p]") MWF_RING("4", "5", "6", "7", SGN, "[q]")       \
+                 MWF_RING("8", "9", "10", "11", SGN, "[r]") MWF_RING("12", "13", "14", "15", SGN, "[s]")           \
+                 : MWF_OUT(0), MWF_OUT(1), MWF_OUT(2), MWF_OUT(3)                                                  \
+                 : MWF_IN, [p] "v"(u[0]), [q] "v"(u[1]), [r] "v"(u[2]), [s] "v"(u[3]));
+template <int V, bool NEG, int R>
+__device__ __forceinline__ void accumulate(double (&er)[R], double (&ei)[R], double (&orr)[R], double (&oi)[R],
+                                           const double (&u)[R], double bx, double by) {
+  static_assert(R == 1 || R == 2 || R == 4, "ring pairs per lane");
+  if constexpr (NEG) {
+    MWF_ACCUMULATE("-")
+  } else {
+    MWF_ACCUMULATE("")
+  }
+}
+#undef MWF_ACCUMULATE
+#undef MWF_IN
+#undef MWF_OUT
+#undef MWF_RING
+#undef MWF_FMAC
+
+template <int R, int FORM>
+__device__ __forceinline__ void synthesis_item(const PlanDev& P, const Leg64Dev& L, const int k, const Item64 it,
+                                               const int map, const int lane, double* __restrict__ sA,
+                                               const double2* __restrict__ bcoef, double* __restrict__ F) {
+  const int m = it.m, blk = it.blk;
+  const int64_t roff = P.row_off[m] + it.i0;
+  const double* __restrict__ Arow = L.ab[FORM] + roff;
+  const double2* __restrict__ brow = bcoef + (size_t)map * P.rows_total + roff;
+  const int nact = P.n_active[m];
+  const int nl = it.i1 - it.i0;
+  // recurrence coefficients of LTILE values of l: lane i loads l = base + i one tile ahead,
+  // the tile in use is read from LDS (the same address in every lane); synthesis coefficients
+  // of SCH values of l likewise, in registers. The loads are unconditional, with the index
+  // clamped into the row's zero padding.
+  auto tile_a = [&](int i) { return Arow[min(i, nl + 1)]; };
+  auto tile_b = [&](int i) { return brow[min(i + (lane & (SCH - 1)), nl + 1)]; };
+  RingState<R> st;
+  double z[R];
+  init_rings<R, FORM>(P, L.syn, L.z, k, blk, lane, nact, st, z);
+  sA[lane] = tile_a(lane);
+  double2 b = tile_b(0);
+  // every load issued so far (ring states, tile 0) completes here
+  __builtin_amdgcn_s_waitcnt(0);
+  wave_sync();
+  double An = tile_a(LTILE + lane);
+  double Ere[R], Eim[R], Ore[R], Oim[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) Ere[r] = Eim[r] = Ore[r] = Oim[r] = 0.0;
+
+  for (int i = 0; i < nl; i += SCH) {
+    const int t0 = i & (LTILE - 1);
+    if (t0 == 0 && i > 0) {
+      wave_sync();
+      sA[lane] = An;
+      wave_sync();
+      An = tile_a(i + LTILE + lane);
+    }
+    const double2 bn = tile_b(i + SCH);
+    const unsigned scaled = st.sc;
+    const double2* Ac = reinterpret_cast<const double2*>(sA + t0);
+    auto step = [&](auto V) {
+      constexpr int v = decltype(V)::value;     // slots v, v + 1 (k even) and v + 2, v + 3 (k odd)
+      const double2 c0 = Ac[v / 2], c1 = Ac[v / 2 + 1];
+      double u[2][R];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        step_pair<FORM>(st.u1[r], st.u2[r], st.zz[r], c0, c1, [&](int h, double x) { u[h][r] = x; });
+      accumulate<v, false>(Ere, Eim, Ore, Oim, u[0], b.x, b.y);
+      accumulate<v + 2, FORM == EQ>(Ere, Eim, Ore, Oim, u[1], b.x, b.y);
+    };
+    step(std::integral_constant<int, 0>());
+    step(std::integral_constant<int, 4>());
+    step(std::integral_constant<int, 8>());
+    step(std::integral_constant<int, 12>());
+    b = bn;
+    // a ring still scaled at the chunk start has contributed nothing so far: clear it
+    if (wave_any(scaled != 0)) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (scaled & (0xffu << (8 * r))) Ere[r] = Eim[r] = Ore[r] = Oim[r] = 0.0;
+      rescale_chunk<R>(st);
+    }
+  }
+
+  const size_t pstride = gf_stride(P.lmax);
+  double* Fm = F + (size_t)map * P.npairs * pstride + (size_t)m * 4;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int q = blk * (LANES * R) + r * LANES + lane;
+    if (q < nact)
+      *reinterpret_cast<double4*>(Fm + (size_t)q * pstride) =
+          make_double4(Ere[r], Eim[r], z[r] * Ore[r], z[r] * Oim[r]);
+  }
+  wave_sync();   // the next item's tile 0 is written after this one's last reads
+}
 
 template <int R>
-__global__ void __launch_bounds__(FP64_WG_WAVES * LANES) legendre_synthesis_f64_kernel(
-    PlanDev P, const WorkItem* __restrict__ items, const int32_t* __restrict__ bins, int nbins, SynthArgs a) {
-  // per-wave LDS: the waves of a workgroup run unrelated bins and never synchronise
-  __shared__ double sA_w[FP64_WG_WAVES][LTILE];
-  __shared__ double2 sb_w[FP64_WG_WAVES][LTILE];
-  const int wave = threadIdx.x / LANES;
-  const int bin = blockIdx.x * FP64_WG_WAVES + wave;
-  if (bin >= nbins) return;
-  double* sA = sA_w[wave];
-  double2* sb = sb_w[wave];
-  const int map = blockIdx.y;
-  // this wave's bin of work items (packed at plan time)
-  const int k_end = bins[bin + 1];
-  for (int k = bins[bin]; k < k_end; ++k) {
-    const WorkItem it = items[k];
-    const int m = it.m, blk = it.blk;
-    const int lane = threadIdx.x % LANES;
-    const int lmax = P.lmax;
-    const int64_t roff = P.row_off[m];
-    const double* __restrict__ Arow = P.A + roff;
-    const double2* __restrict__ brow = a.bcoef + (size_t)map * P.rows_total + roff;
-
-    const int nact = P.n_active[m];
-    const int nl = lmax - m + 1;
-    // coefficients of LTILE values of l: lane i loads l = base + i one tile ahead,
-    // the tile in use is read from LDS (the same address in every lane). The loads
-    // are unconditional, with the index clamped to nl (the first entry of the row's
-    // zero padding: A is zero there and the coefficient kernel writes zeros past
-    // lmax), so that no wait for them lands inside the loop.
-    auto tile_a = [&](int i) { return Arow[min(i, nl)]; };
-    auto tile_b = [&](int i) { return brow[min(i, nl)]; };
-    RingState<R> st;
-    init_rings<R>(P, m, blk, lane, nact, st);
-    sA[lane] = tile_a(lane);
-    sb[lane] = tile_b(lane);
-    // every load issued so far (ring seeds, tile 0) completes here, so the loop body
-    // waits on nothing but its own LDS reads
-    __builtin_amdgcn_s_waitcnt(0);
-    wave_sync();
-    double An = tile_a(LTILE + lane);
-    double2 bn = tile_b(LTILE + lane);
-    double Ere[R], Eim[R], Ore[R], Oim[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) Ere[r] = Eim[r] = Ore[r] = Oim[r] = 0.0;
-
-    for (int l0 = m; l0 <= lmax; l0 += SCH) {
-      const int t0 = (l0 - m) & (LTILE - 1);
-      if (t0 == 0 && l0 > m) {
-        wave_sync();
-        sA[lane] = An;
-        sb[lane] = bn;
-        wave_sync();
-        An = tile_a(l0 - m + LTILE + lane);
-        bn = tile_b(l0 - m + LTILE + lane);
-      }
-      double A[SCH];
-      double2 b[SCH];
-#pragma unroll
-      for (int j = 0; j < SCH; ++j) {
-        A[j] = sA[t0 + j];
-        b[j] = sb[t0 + j];
-      }
-      int scaled = 0;
-#pragma unroll
-      for (int r = 0; r < R; ++r) scaled |= (st.sc[r] != 0) << r;
-#pragma unroll
-      for (int j = 0; j < SCH; j += 2) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          st.mu2[r] = fma(A[j] * st.z[r], st.mu1[r], -st.mu2[r]);          // l - m even
-          Ere[r] = fma(st.mu2[r], b[j].x, Ere[r]);
-          Eim[r] = fma(st.mu2[r], b[j].y, Eim[r]);
-          st.mu1[r] = fma(A[j + 1] * st.z[r], st.mu2[r], -st.mu1[r]);      // odd
-          Ore[r] = fma(st.mu1[r], b[j + 1].x, Ore[r]);
-          Oim[r] = fma(st.mu1[r], b[j + 1].y, Oim[r]);
-        }
-      }
-      // a ring still scaled at the chunk start has contributed nothing so far: clear it
-      if (wave_any(scaled)) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-          if (scaled & (1 << r)) Ere[r] = Eim[r] = Ore[r] = Oim[r] = 0.0;
-        rescale_chunk<R>(st);
-      }
-    }
-
-    const size_t pstride = gf_stride(lmax);
-    double* Fm = a.F + (size_t)map * P.npairs * pstride + (size_t)m * 4;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int q = blk * (LANES * R) + r * LANES + lane;
-      if (q < nact)
-        *reinterpret_cast<double4*>(Fm + (size_t)q * pstride) =
-            make_double4(Ere[r], Eim[r], Ore[r], Oim[r]);
+__global__ void __launch_bounds__(FP64_SYN_WAVES * LANES) legendre_synthesis_f64_kernel(PlanDev P, Leg64Dev L,
+                                                                      const double2* __restrict__ bcoef,
+                                                                      double* __restrict__ F) {
+  // the queue's counter, then per-wave LDS: waves run unrelated items and never synchronise
+  extern __shared__ __attribute__((aligned(16))) double leg64_lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
+  const int lane = threadIdx.x % LANES;
+  double* sA = leg64_lds + 2 + wave * LTILE;
+  for (ItemQueue q(L.syn, leg64_lds); q.next(lane);) {
+    const int k = q.k;
+    const Item64 it = L.syn.items[k];
+    switch (block_form(P, it.blk, LANES * R)) {
+      case EQ: synthesis_item<R, EQ>(P, L, k, it, blockIdx.y, lane, sA, bcoef, F); break;
+      case CAP: synthesis_item<R, CAP>(P, L, k, it, blockIdx.y, lane, sA, bcoef, F); break;
+      default: synthesis_item<R, MID>(P, L, k, it, blockIdx.y, lane, sA, bcoef, F);
     }
   }
 }
 
 // Plan time, per (m, ring pair): the first l - m + 1 at which lambda_lm(z_q) has
 // risen above the scaled range (its scale reached 0; 0 if it starts there), or
-// WAKE_NEVER if that does not happen for l <= lmax (the pair is skipped for m).
-__global__ void reach_kernel(PlanDev P, uint16_t* __restrict__ wake) {
+// WAKE_NEVER if that does not happen for l <= lmax (the pair is skipped for m); and
+// likewise in `rise` the first l - m at which it exceeds 2^-128.
+__global__ void reach_kernel(PlanDev P, uint16_t* __restrict__ wake, uint16_t* __restrict__ rise) {
   const int m = blockIdx.y;
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= P.npairs) return;
@@ -420,75 +560,117 @@ __global__ void reach_kernel(PlanDev P, uint16_t* __restrict__ wake) {
   double v;
   int s;
   sectoral_seed(m, rp.sin_t, P.norm_m[m], &v, &s);
-  uint16_t w = s == 0 ? 0 : WAKE_NEVER;
-  if (s != 0) {
+  uint16_t w = s == 0 ? 0 : WAKE_NEVER, e = s == 0 && fabs(v) > RISE_THRESH ? 0 : WAKE_NEVER;
+  if (e != 0) {
     const double* Arow = P.A + P.row_off[m];
     double mu1 = 0.0, mu2 = -v;
     for (int l = m; l <= P.lmax; ++l) {
       const double mu = fma(Arow[l - m] * rp.z, mu1, -mu2);
       mu2 = mu1;
       mu1 = mu;
-      if (fabs(mu1) > BIG_THRESH) {
+      if (s > 0 && fabs(mu1) > BIG_THRESH) {
         mu1 *= RESCALE;
         mu2 *= RESCALE;
-        if (--s == 0) {
-          w = (uint16_t)(l - m + 1);
-          break;
-        }
+        if (--s == 0) w = (uint16_t)(l - m + 1);
+      }
+      if (s == 0 && fabs(mu1) > RISE_THRESH) {
+        e = (uint16_t)(l - m);
+        break;
       }
     }
   }
   wake[(size_t)m * P.npairs + q] = w;
+  rise[(size_t)m * P.npairs + q] = e;
+}
+
+// Plan time: the recurrence state of every ring pair of every item at its first l (workgroup k:
+// item k, thread t: pair t of the block), run with the kernels' own steps and scale checks (ch
+// values of l per check; items start at multiples of it).
+__global__ void start_state_kernel(PlanDev P, Leg64Dev L, const Item64* __restrict__ items, int ch,
+                                   double2* __restrict__ state, uint8_t* __restrict__ scale) {
+  const Item64 it = items[blockIdx.x];
+  const int m = it.m, rb = blockDim.x, q = it.blk * rb + threadIdx.x;
+  const size_t at = (size_t)blockIdx.x * rb + threadIdx.x;
+  double u1 = 0.0, u2 = 0.0;
+  int s = 0;
+  if (q < P.n_active[m]) {
+    const int form = block_form(P, it.blk, rb);
+    const RingPair rp = P.pairs[q];
+    double v;
+    sectoral_seed(m, rp.sin_t, P.norm_m[m], &v, &s);
+    u2 = form == MID ? -v : v;     // with zero coefficients in slot 0 the first step yields u_0 = v
+    const double zz = form == CAP ? (1.0 - rp.z) * (1.0 + rp.z) : rp.z * rp.z;
+    const double2* ab = reinterpret_cast<const double2*>(L.ab[form] + P.row_off[m]);
+    auto none = [](int, double) {};
+    for (int i = 0; i < it.i0; i += ch) {
+      for (int j = i / 2; j < (i + ch) / 2; j += 2) {
+        if (form == MID) step_pair<MID>(u1, u2, zz, ab[j], ab[j + 1], none);
+        else step_pair<CAP>(u1, u2, zz, ab[j], ab[j + 1], none);   // (EQ differs in the sign handed out)
+      }
+      if (s > 0 && fmax(fabs(u1), fabs(u2)) > BIG_THRESH) {
+        u1 *= RESCALE;
+        u2 *= RESCALE;
+        s -= 1;
+      }
+    }
+  }
+  state[at] = make_double2(u1, u2);
+  scale[at] = (uint8_t)s;
 }
 
 template <int R>
-hipError_t launch_ana_r(const PlanDev& P, const WorkItem* items, const int32_t* bins, int nbins, int nmaps,
-                        const double* G, double2* partial, hipStream_t s) {
-  hipLaunchKernelGGL(legendre_analysis_f64_kernel<R>, dim3((nbins + FP64_WG_WAVES - 1) / FP64_WG_WAVES, nmaps),
-                     dim3(FP64_WG_WAVES * LANES), 0, s, P, items, bins, nbins, G, partial);
+hipError_t launch_ana_r(const PlanDev& P, const Leg64Dev& L, int nmaps, const double* G, double2* partial,
+                        hipStream_t s) {
+  const size_t lds = ((size_t)L.ana.waves * ANA_LDS + 2) * sizeof(double);
+  if (hipError_t e = ensure_dynamic_lds((const void*)legendre_analysis_f64_kernel<R>, lds)) return e;
+  hipLaunchKernelGGL(legendre_analysis_f64_kernel<R>, dim3(L.ana.nwg, nmaps),
+                     dim3(L.ana.waves * LANES), lds, s, P, L, G, partial);
   return hipGetLastError();
 }
 
 template <int R>
-hipError_t launch_syn_r(const PlanDev& P, const WorkItem* items, const int32_t* bins, int nbins,
-                        const SynthArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(legendre_synthesis_f64_kernel<R>, dim3((nbins + FP64_WG_WAVES - 1) / FP64_WG_WAVES, a.nmaps),
-                     dim3(FP64_WG_WAVES * LANES), 0, s, P, items, bins, nbins, a);
+hipError_t launch_syn_r(const PlanDev& P, const Leg64Dev& L, const SynthArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(legendre_synthesis_f64_kernel<R>, dim3(L.syn.nwg, a.nmaps),
+                     dim3(L.syn.waves * LANES), ((size_t)L.syn.waves * LTILE + 2) * sizeof(double), s, P, L, a.bcoef, a.F);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_legendre_analysis_f64(const PlanDev& P, const WorkItem* items, const int32_t* bins,
-                                        int nbins, int nmaps, const double* G, double2* partial,
-                                        hipStream_t s) {
-  switch (P.ring_block_ana / LANES) {
-    case 1: return launch_ana_r<1>(P, items, bins, nbins, nmaps, G, partial, s);
-    case 2: return launch_ana_r<2>(P, items, bins, nbins, nmaps, G, partial, s);
-    case 4: return launch_ana_r<4>(P, items, bins, nbins, nmaps, G, partial, s);
+hipError_t launch_legendre_analysis_f64(const PlanDev& P, const Leg64Dev& L, int nmaps, const double* G,
+                                        double2* partial, hipStream_t s) {
+  switch (L.ana.rb / LANES) {
+    case 1: return launch_ana_r<1>(P, L, nmaps, G, partial, s);
+    case 2: return launch_ana_r<2>(P, L, nmaps, G, partial, s);
+    case 4: return launch_ana_r<4>(P, L, nmaps, G, partial, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_legendre_coeff(const PlanDev& P, const SynthArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(legendre_coeff_kernel, dim3((unsigned)((P.rows_total + 255) / 256), a.nmaps), dim3(256), 0, s,
-                     P, a);
+hipError_t launch_legendre_coeff(const PlanDev& P, const Leg64Dev& L, const SynthArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(legendre_coeff_kernel, dim3((unsigned)((P.rows_total + COEFF_ROWS - 1) / COEFF_ROWS), a.nmaps),
+                     dim3(COEFF_WG), 0, s, P, L, a);
   return hipGetLastError();
 }
 
-hipError_t launch_legendre_synthesis_f64(const PlanDev& P, const WorkItem* items, const int32_t* bins,
-                                         int nbins, const SynthArgs& a, hipStream_t s) {
-  switch (P.ring_block_syn / LANES) {
-    case 1: return launch_syn_r<1>(P, items, bins, nbins, a, s);
-    case 2: return launch_syn_r<2>(P, items, bins, nbins, a, s);
-    case 4: return launch_syn_r<4>(P, items, bins, nbins, a, s);
+hipError_t launch_legendre_synthesis_f64(const PlanDev& P, const Leg64Dev& L, const SynthArgs& a, hipStream_t s) {
+  switch (L.syn.rb / LANES) {
+    case 1: return launch_syn_r<1>(P, L, a, s);
+    case 2: return launch_syn_r<2>(P, L, a, s);
+    case 4: return launch_syn_r<4>(P, L, a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_reach(const PlanDev& P, uint16_t* wake, hipStream_t s) {
+hipError_t launch_reach(const PlanDev& P, uint16_t* wake, uint16_t* rise, hipStream_t s) {
   dim3 grid((P.npairs + 127) / 128, P.lmax + 1);
-  hipLaunchKernelGGL(reach_kernel, grid, dim3(128), 0, s, P, wake);
+  hipLaunchKernelGGL(reach_kernel, grid, dim3(128), 0, s, P, wake, rise);
+  return hipGetLastError();
+}
+
+hipError_t launch_start_state(const PlanDev& P, const Leg64Dev& L, const Leg64List& T, int nitems, int ch,
+                              double2* state, uint8_t* scale, hipStream_t s) {
+  hipLaunchKernelGGL(start_state_kernel, dim3(nitems), dim3(T.rb), 0, s, P, L, T.items, ch, state, scale);
   return hipGetLastError();
 }
 

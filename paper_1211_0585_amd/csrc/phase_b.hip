@@ -43,6 +43,24 @@
 #include "mwf_internal.hpp"
 
 namespace mwf {
+
+// Raise the dynamic-LDS limit of `kernel` on the current device to at least `lds`
+// (never lower it). One lock for every kernel and device: launches of one kernel
+// from several host threads (plans, the server's stepping thread) must not undo
+// each other's limit.
+hipError_t ensure_dynamic_lds(const void* kernel, size_t lds) {
+  static std::mutex mu;
+  static std::map<std::pair<const void*, int>, size_t> limit;
+  int dev = 0;
+  if (hipError_t e = hipGetDevice(&dev)) return e;
+  std::lock_guard<std::mutex> lock(mu);
+  size_t& cur = limit[{kernel, dev}];
+  if (lds <= cur) return hipSuccess;
+  if (hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) return e;
+  cur = lds;
+  return hipSuccess;
+}
+
 namespace {
 
 // Rings of at most FOLD_PARTS points fold their aliases with FOLD_PARTS / n partial
@@ -1069,23 +1087,6 @@ constexpr int ring_threads(int cls) { return cls == 0 ? 512 : (cls == 1 ? 256 : 
 int maxb_for(int fft_len, int nt) {
   const int b = (fft_len + 4 * nt - 1) / (4 * nt);
   return b <= 1 ? 1 : (b <= 2 ? 2 : (b <= 4 ? 4 : 0));
-}
-
-// Raise the dynamic-LDS limit of `kernel` on the current device to at least `lds`
-// (never lower it). One lock for every kernel and device: launches of one kernel
-// from several host threads (plans, the server's stepping thread) must not undo
-// each other's limit.
-hipError_t ensure_dynamic_lds(const void* kernel, size_t lds) {
-  static std::mutex mu;
-  static std::map<std::pair<const void*, int>, size_t> limit;
-  int dev = 0;
-  if (hipError_t e = hipGetDevice(&dev)) return e;
-  std::lock_guard<std::mutex> lock(mu);
-  size_t& cur = limit[{kernel, dev}];
-  if (lds <= cur) return hipSuccess;
-  if (hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) return e;
-  cur = lds;
-  return hipSuccess;
 }
 
 template <class T, class C, int NT, int MAXB, int CLS>

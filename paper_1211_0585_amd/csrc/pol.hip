@@ -348,79 +348,108 @@ __global__ void __launch_bounds__(S2_WAVES * LANES) spin2_synthesis_kernel(PlanD
   }
 }
 
-// One thread per (l, m, map), rows padded as the recurrence tables:
-//   a_T = C_l sum partial_T,  a_E = -(K/2) sum partial_E,  a_B = (K/2) sum partial_B
+// One thread per (l, m, map) over the padded rows of the recurrence tables, on the flat grid with
+// two halo rows on either side that the spin-0 coefficient kernel has (i = l - m, P_i the sums
+// of the T blocks, alpha and beta the factors of the two-step recurrence):
+//   a_T = alpha_i P_i + beta_i P_{i-2},  a_E = -(K/2) sum partial_E,  a_B = (K/2) sum partial_B
 //   SY_FROM_PARTIAL: s = F_l a with F_l = C_l (C_l + lambda tau Omega)^-1 (TE-coupled),
-//   SY_ALM_ONLY: s = a,  SY_FROM_ALM: s = the caller's alm (imaginary part dropped at m = 0).
+//   SY_ALM_ONLY: s = a,  SY_FROM_ALM: s = the caller's alm (imaginary part dropped at m = 0),
+// and bcoef_t = alpha_i s_T,i + beta_{i+2} s_T,i+2.
 // F_l in closed form for the TE block [[TT, TE], [TE, EE]] (mu = lambda tau Omega,
 // det = TT EE - TE^2, D = det + mu (TT + EE) + mu^2):
 //   F_TT = (det + TT mu) / D, F_TE = TE mu / D, F_EE = (det + EE mu) / D, F_BB = BB / (BB + mu)
 // (no cancellation, and 0 where the spectra vanish).
-__global__ void pol_coeff_kernel(PlanDev P, Spin2Dev S2, PolCoeffArgs a) {
-  const int m = blockIdx.x;
+constexpr int PC_WG = 256, PC_ROWS = PC_WG - 4;
+
+__global__ void __launch_bounds__(PC_WG) pol_coeff_kernel(PlanDev P, Leg64Dev L, Spin2Dev S2, PolCoeffArgs a) {
+  __shared__ double2 sP[PC_WG], sS[PC_WG];
+  const int t = threadIdx.x;
+  const int64_t r = (int64_t)blockIdx.x * PC_ROWS + t - 2;
   const int map = blockIdx.y;
+  const bool own = t >= 2 && t < 2 + PC_ROWS && r < P.rows_total;
   const int lmax = P.lmax;
-  const int nl = lmax - m + 1;
-  const int64_t row = alm_index(lmax, m, m);
-  const int64_t roff = P.row_off[m];
   const double mu = a.lambda * P.tau * P.omega;
-  const int nbt = P.nblk[m];
-  const int nbe = a.nblk2_m[m];
-  for (int i = threadIdx.x; i < nl + ROW_PAD; i += blockDim.x) {
-    double2 sT = make_double2(0, 0), sE = sT, sB = sT;
-    double K = 0.0, C0 = 0.0;
-    if (i < nl) {
-      const int l = m + i;
-      K = S2.K[roff + i];
-      C0 = P.C[roff + i];
-      if (a.mode == SY_FROM_ALM) {
-        const double2* al = a.alm_in + (size_t)map * 3 * P.nalm + row + i;
-        sT = al[0];
-        sE = al[P.nalm];
-        sB = al[2 * P.nalm];
-        if (m == 0) sT.y = sE.y = sB.y = 0.0;
-      } else {
-        double tr = 0, ti = 0;
-        for (int k = 0; k < nbt; ++k) {
-          const double2 p = a.partial_t[((size_t)map * P.nblk_max + k) * P.nalm + row + i];
-          tr += p.x;
-          ti += p.y;
-        }
-        double er = 0, ei = 0, br = 0, bi = 0;
-        for (int k = 0; k < nbe; ++k) {
-          const double4 p = reinterpret_cast<const double4*>(a.partial_eb)[((size_t)map * a.nblk2 + k) * P.nalm + row + i];
-          er += p.x;
-          ei += p.y;
-          br += p.z;
-          bi += p.w;
-        }
-        sT = make_double2(tr * C0, ti * C0);
-        sE = make_double2(-0.5 * K * er, -0.5 * K * ei);
-        sB = make_double2(0.5 * K * br, 0.5 * K * bi);
-        if (a.mode == SY_FROM_PARTIAL) {
-          const double tt = a.cl4[l], ee = a.cl4[(lmax + 1) + l], bb = a.cl4[2 * (lmax + 1) + l];
-          const double te = a.cl4[3 * (lmax + 1) + l];
-          const double det = tt * ee - te * te;
-          const double D = det + mu * (tt + ee) + mu * mu;
-          const double ftt = (det + tt * mu) / D, fte = te * mu / D, fee = (det + ee * mu) / D;
-          const double fbb = bb > 0.0 ? bb / (bb + mu) : 0.0;
-          const double2 t2 = make_double2(ftt * sT.x + fte * sE.x, ftt * sT.y + fte * sE.y);
-          const double2 e2 = make_double2(fte * sT.x + fee * sE.x, fte * sT.y + fee * sE.y);
-          sT = t2;
-          sE = e2;
-          sB = make_double2(fbb * sB.x, fbb * sB.y);
-        }
+  int m = 0, i = 0;
+  bool val = false;
+  double2 co = make_double2(0.0, 0.0);
+  double K = 0.0;
+  if (r >= 0 && r < P.rows_total) {
+    m = P.row_m[r];
+    i = (int)(r - P.row_off[m]);
+    val = i < lmax - m + 1;
+    if (val) {
+      co = L.co[r];
+      K = S2.K[r];
+    }
+  }
+  const int l = m + i;
+  const int64_t at = alm_index(lmax, m, m) + i;
+  double2 sT = make_double2(0, 0), sE = sT, sB = sT;
+  if (a.mode == SY_FROM_ALM) {
+    if (val) {
+      const double2* al = a.alm_in + (size_t)map * 3 * P.nalm + at;
+      sT = al[0];
+      sE = al[P.nalm];
+      sB = al[2 * P.nalm];
+      if (m == 0) sT.y = sE.y = sB.y = 0.0;
+    }
+  } else {
+    double2 p = make_double2(0, 0);
+    if (val) p = block_partials(P, L, a.partial_t + (size_t)map * P.nblk_max * P.nalm + at, m, i);
+    sP[t] = p;
+    __syncthreads();
+    if (val && t >= 2) {
+      const int nbe = a.nblk2_m[m];
+      double er = 0, ei = 0, br = 0, bi = 0;
+      for (int k = 0; k < nbe; ++k) {
+        const double4 e = reinterpret_cast<const double4*>(a.partial_eb)[((size_t)map * a.nblk2 + k) * P.nalm + at];
+        er += e.x;
+        ei += e.y;
+        br += e.z;
+        bi += e.w;
       }
-      if (a.alm_out) {
-        double2* ao = a.alm_out + (size_t)map * 3 * P.nalm + row + i;
-        ao[0] = sT;
-        ao[P.nalm] = sE;
-        ao[2 * P.nalm] = sB;
+      sT = make_double2(co.x * p.x, co.x * p.y);
+      if (co.y != 0.0) {
+        const double2 q = sP[t - 2];
+        sT.x = fma(co.y, q.x, sT.x);
+        sT.y = fma(co.y, q.y, sT.y);
+      }
+      sE = make_double2(-0.5 * K * er, -0.5 * K * ei);
+      sB = make_double2(0.5 * K * br, 0.5 * K * bi);
+      if (a.mode == SY_FROM_PARTIAL) {
+        const double tt = a.cl4[l], ee = a.cl4[(lmax + 1) + l], bb = a.cl4[2 * (lmax + 1) + l];
+        const double te = a.cl4[3 * (lmax + 1) + l];
+        const double det = tt * ee - te * te;
+        const double D = det + mu * (tt + ee) + mu * mu;
+        const double ftt = (det + tt * mu) / D, fte = te * mu / D, fee = (det + ee * mu) / D;
+        const double fbb = bb > 0.0 ? bb / (bb + mu) : 0.0;
+        const double2 t2 = make_double2(ftt * sT.x + fte * sE.x, ftt * sT.y + fte * sE.y);
+        const double2 e2 = make_double2(fte * sT.x + fee * sE.x, fte * sT.y + fee * sE.y);
+        sT = t2;
+        sE = e2;
+        sB = make_double2(fbb * sB.x, fbb * sB.y);
       }
     }
-    if (a.mode != SY_ALM_ONLY) {
-      a.bcoef_t[(size_t)map * P.rows_total + roff + i] = make_double2(sT.x * C0, sT.y * C0);
-      double2* be = a.bcoef_eb + ((size_t)map * P.rows_total + roff + i) * 2;
+  }
+  if (own && val && a.alm_out) {
+    double2* ao = a.alm_out + (size_t)map * 3 * P.nalm + at;
+    ao[0] = sT;
+    ao[P.nalm] = sE;
+    ao[2 * P.nalm] = sB;
+  }
+  if (a.mode != SY_ALM_ONLY) {
+    sS[t] = sT;
+    __syncthreads();
+    if (own) {
+      double2 b = make_double2(co.x * sT.x, co.x * sT.y);
+      const double beta = val ? L.co[r + 2].y : 0.0;   // (a row ends in padding: r + 2 stays inside it)
+      if (beta != 0.0) {
+        const double2 n = sS[t + 2];
+        b.x = fma(beta, n.x, b.x);
+        b.y = fma(beta, n.y, b.y);
+      }
+      a.bcoef_t[(size_t)map * P.rows_total + r] = b;
+      double2* be = a.bcoef_eb + ((size_t)map * P.rows_total + r) * 2;
       be[0] = make_double2(-0.5 * K * sE.x, -0.5 * K * sE.y);
       be[1] = make_double2(-0.5 * K * sB.x, -0.5 * K * sB.y);
     }
@@ -444,8 +473,10 @@ hipError_t launch_spin2_synthesis(const PlanDev& P, const Spin2Dev& S2, int nmap
   return hipGetLastError();
 }
 
-hipError_t launch_pol_coeff(const PlanDev& P, const Spin2Dev& S2, const PolCoeffArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(pol_coeff_kernel, dim3(P.lmax + 1, a.nmaps), dim3(256), 0, s, P, S2, a);
+hipError_t launch_pol_coeff(const PlanDev& P, const Leg64Dev& L, const Spin2Dev& S2, const PolCoeffArgs& a,
+                            hipStream_t s) {
+  hipLaunchKernelGGL(pol_coeff_kernel, dim3((unsigned)((P.rows_total + PC_ROWS - 1) / PC_ROWS), a.nmaps), dim3(PC_WG), 0,
+                     s, P, L, S2, a);
   return hipGetLastError();
 }
 

@@ -147,7 +147,7 @@ int pol_ring(wf_pol_plan_s* p, hipStream_t s, int mode, int nmaps, double lam, c
 int pol_analysis(wf_pol_plan_s* p, hipStream_t s, int nmaps, PolTimer& tm) {
   const Geometry& g = *p->geo;
   POL_TIMED(tm, 1, {
-    MWF_HIP(launch_legendre_analysis_f64(p->dev, g.items_ana, g.bins_ana, g.nbins_ana, nmaps, p->G, p->partial_t, s));
+    MWF_HIP(launch_legendre_analysis_f64(p->dev, g.leg64, nmaps, p->G, p->partial_t, s));
     MWF_HIP(launch_spin2_analysis(p->dev, p->s2, nmaps, p->G, p->partial_eb, p->nblk2, s));
   });
   return WF_OK;
@@ -175,9 +175,9 @@ int pol_synthesis(wf_pol_plan_s* p, hipStream_t s, int mode, int nmaps, double l
   a.bcoef = p->bcoef_t;
   a.F = p->F;
   POL_TIMED(tm, 2, {
-    MWF_HIP(launch_pol_coeff(p->dev, p->s2, c, s));
+    MWF_HIP(launch_pol_coeff(p->dev, g.leg64, p->s2, c, s));
     if (mode != SY_ALM_ONLY) {
-      MWF_HIP(launch_legendre_synthesis_f64(p->dev, g.items_syn, g.bins_syn, g.nbins_syn, a, s));
+      MWF_HIP(launch_legendre_synthesis_f64(p->dev, g.leg64, a, s));
       MWF_HIP(launch_spin2_synthesis(p->dev, p->s2, nmaps, p->bcoef_eb, p->F, s));
     }
   });
@@ -282,7 +282,7 @@ int wf_pol_plan(wf_pol_plan_t* out, int32_t nside, int32_t lmax, const double* c
   if (!(nmax > 0)) return fail(WF_EINVAL, "no observed pixel (N^-1 zero everywhere after masking)");
 
   std::shared_ptr<Geometry> geo;
-  if (int rc = get_geometry(nside, lmax, &geo)) return rc;
+  if (int rc = get_geometry(nside, lmax, true, &geo)) return rc;
   auto* p = new wf_pol_plan_s();
   auto bail = [&](int code) {
     wf_pol_destroy(p);
@@ -353,7 +353,6 @@ int wf_pol_plan(wf_pol_plan_t* out, int32_t nside, int32_t lmax, const double* c
   D.tau = p->tau;
   D.omega = g.omega;
   D.ring_block_ana = g.ring_block_ana;
-  D.ring_block_syn = g.ring_block_syn;
   D.nblk_max = g.nblk_max_ana;
   D.pairs = g.pairs;
   D.q = p->q6;

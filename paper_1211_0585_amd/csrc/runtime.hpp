@@ -68,7 +68,7 @@ struct Geometry {
   int64_t units_active = 0;
   std::vector<int32_t> n_active;       // per m
   // FP64 VALU path
-  int ring_block_ana = 64, ring_block_syn = 64, nblk_max_ana = 1;
+  int ring_block_ana = 64, nblk_max_ana = 1;
   // device tables
   RingPair* pairs = nullptr;
   double* A = nullptr;
@@ -86,17 +86,15 @@ struct Geometry {
   float2* blue32 = nullptr;
   double2* mixtw = nullptr;            // mixed-radix ring tables exp(-2 pi i t / n)
   float2* mixtw32 = nullptr;
-  // work lists, longest first
-  WorkItem* items_ana = nullptr;       // FP64 analysis (ring_block_ana), packed into bins
-  WorkItem* items_syn = nullptr;       // FP64 synthesis (ring_block_syn), packed into bins
-  int32_t* bins_ana = nullptr;         // [nbins + 1] item range of each wave of an FP64 launch
-  int32_t* bins_syn = nullptr;
-  int nbins_ana = 0, nbins_syn = 0;
+  // FP64 Legendre tables and work lists, made by the first FP64 or polarised plan of the shape
+  bool leg64_ready = false;
+  Leg64Dev leg64{};
   int n_cu = 0;                        // compute units of the device
-  WorkItem* items_a128 = nullptr;      // matrix-core analysis, 128 / 256 ring pairs
+  // matrix-core work lists, longest first
+  WorkItem* items_a128 = nullptr;      // analysis, 128 / 256 ring pairs
   WorkItem* items_a256 = nullptr;
-  WorkItem* items_s64 = nullptr;       // matrix-core synthesis, 64 ring pairs
-  int n_ana = 0, n_syn = 0, n_a128 = 0, n_a256 = 0, n_s64 = 0;
+  WorkItem* items_s64 = nullptr;       // synthesis, 64 ring pairs
+  int n_a128 = 0, n_a256 = 0, n_s64 = 0;
   // ring launch classes: [0] one or few maps (Bluestein, power of two), [1] from
   // RING_SPLIT_MAPS maps on (long Bluestein, long power of two, short)
   RingClass ring_cls[2][NRING_CLASSES]{};
@@ -110,7 +108,8 @@ struct Geometry {
   DevMem mem;
 };
 
-int get_geometry(int nside, int lmax, std::shared_ptr<Geometry>* out);
+// fp64: with the FP64 Legendre tables (leg64 and the bins).
+int get_geometry(int nside, int lmax, bool fp64, std::shared_ptr<Geometry>* out);
 
 // One HEALPix ring (RING order, 1 <= i <= 4 nside - 1): z = cos(theta), first
 // pixel index, pixel count and the longitude of its first pixel, pi ph_num / ph_den.
@@ -160,7 +159,7 @@ TaskDev make_task(wf_plan_s* p, int nmaps, int pb_mode, int sy_mode, double lam,
 int run_group_step(const TaskDev* tasks, const int64_t* offs, const int64_t* nblocks, const int* fft_len,
                    int ntasks, int dtype, const Tuning& tune, bool synth_only, hipStream_t s);
 size_t plan_buffer_bytes(int nside, int lmax, int dtype, int nmaps);
-size_t geometry_bytes(int nside, int lmax);
+size_t geometry_bytes(int nside, int lmax, bool fp64);
 // Constrained realisations: out (+)= sqrt(C_l) xi over nmaps packed alm sets; the data
 // map d - s_rand - eta sqrt(tau / q); out += s_rand.
 hipError_t launch_cr_alm(const double* cl, int lmax, int64_t nalm, int nmaps, const void* xi, void* out,

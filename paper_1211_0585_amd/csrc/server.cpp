@@ -152,7 +152,7 @@ struct wf_server_s {
 
   size_t new_lane_cost(const Request& r) const {
     size_t c = lane_bytes(r.nside, r.lmax, r.dtype, lane_cap(r.nside, r.lmax, r.dtype));
-    if (!geometries.count({r.nside, r.lmax})) c += geometry_bytes(r.nside, r.lmax);
+    if (!geometries.count({r.nside, r.lmax})) c += geometry_bytes(r.nside, r.lmax, false);
     return c;
   }
 
@@ -171,7 +171,7 @@ struct wf_server_s {
               return l->nside == shape.first && l->lmax == shape.second;
             })) {
           geometries.erase(shape);
-          used -= geometry_bytes(shape.first, shape.second);
+          used -= geometry_bytes(shape.first, shape.second, false);
         }
       } else {
         ++it;
@@ -182,7 +182,7 @@ struct wf_server_s {
 
   int create_lane(const Request& r, Lane** out) {
     std::shared_ptr<Geometry> geo;
-    if (int rc = get_geometry(r.nside, r.lmax, &geo)) return rc;
+    if (int rc = get_geometry(r.nside, r.lmax, false, &geo)) return rc;
     auto lane = std::make_unique<Lane>();
     lane->nside = r.nside;
     lane->lmax = r.lmax;
@@ -610,7 +610,7 @@ int wf_server_submit(wf_server_t s, int32_t nside, int32_t lmax, const double* c
   if (s->fatal) return fail(s->fatal, "server stopped: " + s->fatal_msg);
   {
     const int cap1 = 1;
-    size_t need = lane_bytes(nside, lmax, dtype, cap1) + geometry_bytes(nside, lmax);
+    size_t need = lane_bytes(nside, lmax, dtype, cap1) + geometry_bytes(nside, lmax, false);
     if (need > s->budget) return fail(WF_ENOMEM, "request does not fit the server's HBM budget");
   }
   r.ticket = s->next_ticket++;

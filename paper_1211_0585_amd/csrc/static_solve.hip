@@ -141,13 +141,13 @@ extern "C" int wf_solve_batch_static(wf_plan_t p, int32_t nmaps, const void* d, 
     if (int rc = ring(mode, lambda[k], d, nullptr)) return rc;
     void* alm_out = (k == nsweeps - 1) ? s_alm : nullptr;
     if (fp64) {
-      MWF_HIP(launch_legendre_analysis_f64(P, g.items_ana, g.bins_ana, g.nbins_ana, nmaps, static_cast<const double*>(G),
+      MWF_HIP(launch_legendre_analysis_f64(P, g.leg64, nmaps, static_cast<const double*>(G),
                                            reinterpret_cast<double2*>(ws + L.part_off), s));
       sa.mode = SY_FROM_PARTIAL;
       sa.lambda = lambda[k];
       sa.alm_out = static_cast<double2*>(alm_out);
-      MWF_HIP(launch_legendre_coeff(P, sa, s));
-      MWF_HIP(launch_legendre_synthesis_f64(P, g.items_syn, g.bins_syn, g.nbins_syn, sa, s));
+      MWF_HIP(launch_legendre_coeff(P, g.leg64, sa, s));
+      MWF_HIP(launch_legendre_synthesis_f64(P, g.leg64, sa, s));
     } else {
       const int ct = p->tune.ana_ct;
       MWF_HIP(launch_mfma_analysis(P, ct == 1 ? g.items_a128 : g.items_a256, ct == 1 ? g.n_a128 : g.n_a256, p->dtype,
