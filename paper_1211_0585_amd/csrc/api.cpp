@@ -1168,7 +1168,7 @@ void task_offsets(const TaskDev* tasks, const std::vector<const Geometry*>& geos
       const Geometry& g = *geos[t];
       const int nm = tasks[t].nmaps;
       if (ph < NRING_CLASSES) {
-        acc += (int64_t)tasks[t].ring_n[ph] * nm;
+        acc += ring_blocks(tasks[t].ring_n[ph], nm);
         const int split = nm >= RING_SPLIT_MAPS ? 1 : 0;
         if (tasks[t].ring_n[ph]) fft_len[ph] = std::max(fft_len[ph], g.ring_cls[split][ph].fft_len);
         continue;

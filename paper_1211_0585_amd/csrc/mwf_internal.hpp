@@ -283,6 +283,12 @@ struct RingClass {
   int32_t fft_len;
 };
 
+// Blocks of a ring launch over count ring pairs and nmaps maps (with several maps eight ring pairs
+// side by side, one per XCD).
+inline int64_t ring_blocks(int count, int nmaps) {
+  return nmaps == 1 ? count : (int64_t)((count + 7) / 8) * 8 * nmaps;
+}
+
 // Ring launches: class 0 rings that are not a power of two (Bluestein and mixed radix,
 // 512 threads) and class 1 power-of-two rings (256 threads), class 2 transforms of at
 // most 1024 points (one wave per ring pair; used from RING_SPLIT_MAPS maps on, when
@@ -320,6 +326,17 @@ __host__ __device__ inline int fft_twiddle_entries(int lg) {
   return e;
 }
 
+// Further entries of a Bluestein ring: the passes 1 .. n2 + n4 of its inverse transform, whose
+// radices are 8, the n2 2s, the n4 4s, then the other 8s (at most 8 + 32).
+__host__ __device__ inline int blue_twiddle_entries(int lg) {
+  int n2, n4, n8;
+  fft_schedule(lg, &n2, &n4, &n8);
+  int ns = 8, e = 0;
+  for (int p = 0; p < n2; ++p, ns *= 2) e += ns;
+  for (int p = 0; p < n4; ++p, ns *= 4) e += ns;
+  return e;
+}
+
 // Points of the FFT buffer in LDS including the padding of the layout between
 // passes (one element after every 16).
 __host__ __device__ inline int fft_padded(int len) { return len + (len >> 4); }
@@ -330,7 +347,7 @@ __host__ __device__ inline int fft_padded(int len) { return len + (len >> 4); }
 inline size_t ring_lds_bytes(int fft_len, size_t elem) {
   int lg = 0;
   while ((1 << lg) < fft_len) ++lg;
-  const size_t b = ((size_t)fft_padded(fft_len) + (size_t)fft_twiddle_entries(lg)) * elem;
+  const size_t b = ((size_t)fft_padded(fft_len) + (size_t)fft_twiddle_entries(lg) + (size_t)blue_twiddle_entries(lg)) * elem;
   return b < 8192 ? 8192 : b;
 }
 

@@ -30,12 +30,12 @@
 // store maps and ring coefficients in float. Ring pairs are launched in classes:
 // rings that are not a power of two (mixed radix and Bluestein) and power-of-two rings
 // separately (512 and 256 threads, LDS sized to the class: the Bluestein length is about
-// twice the ring's, and a mixed-radix ring counts twice its length), and, from 4 maps
-// on, transforms of at most 1024 points one wave per ring pair, so short polar
+// twice the ring's, and a mixed-radix ring counts twice its length; from 4 maps on, 256 threads
+// where those take at most 2048 points), and, from 4 maps on, transforms of at most 1024 points one wave per ring pair, so short polar
 // rings do not leave most of a large workgroup idle. Each workgroup stages the
 // twiddles of its ring's transform in LDS next to the data, one table per pass
-// read by consecutive lanes at consecutive entries, and the data sit in a padded
-// layout between passes: both keep the passes' LDS accesses off shared banks.
+// read by consecutive lanes at consecutive entries, and from 128 points on the data sit
+// in a padded layout between passes: both keep the passes' LDS accesses off shared banks.
 #include <map>
 #include <mutex>
 #include <utility>
@@ -66,7 +66,6 @@ namespace {
 // Rings of at most FOLD_PARTS points fold their aliases with FOLD_PARTS / n partial
 // sums per bin (see the loading step of phase_b_body).
 constexpr int FOLD_PARTS = 256;
-
 
 template <class C>
 struct CT;
@@ -116,11 +115,10 @@ __device__ __forceinline__ V cmul_is(V a, S s) {
   return r;
 }
 
-// exp(i pi num / den) with the argument reduced exactly (in FP64, then rounded to C).
+// exp(i pi num / den), num >= 0, with the argument reduced exactly (in FP64, then rounded to C).
 template <class C>
-__device__ __forceinline__ typename CT<C>::V expipi(int64_t num, int64_t den) {
-  int64_t r = num % (2 * den);
-  if (r < 0) r += 2 * den;
+__device__ __forceinline__ typename CT<C>::V expipi(unsigned num, unsigned den) {
+  const unsigned r = num % (2 * den);
   double s, c;
   sincospi((double)r / (double)den, &s, &c);
   return CT<C>::make((C)c, (C)s);
@@ -219,32 +217,76 @@ __device__ __forceinline__ void dft_odd(V* u, S sd) {
   for (int r = 0; r < R; ++r) u[r] = y[r];
 }
 
+// u[r] *= w^r (w conjugated for dir = +1), the powers by products at most three deep.
+template <int R, class V>
+__device__ __forceinline__ void twiddle(V* u, V w, int dir) {
+  if (dir > 0) w.y = -w.y;
+  u[1] = cmul(u[1], w);
+  if constexpr (R >= 4) {
+    const V w2 = cmul(w, w), w3 = cmul(w, w2);
+    u[2] = cmul(u[2], w2);
+    u[3] = cmul(u[3], w3);
+    if constexpr (R == 8) {
+      const V w4 = cmul(w2, w2);
+      u[4] = cmul(u[4], w4);
+      u[5] = cmul(u[5], cmul(w, w4));
+      u[6] = cmul(u[6], cmul(w2, w4));
+      u[7] = cmul(u[7], cmul(w3, w4));
+    }
+  }
+}
+
+// Radix-R DFT of u in registers, R = 2, 4 or 8.
+template <int R, class V, class S>
+__device__ __forceinline__ void butterfly(V* u, S sd) {
+  if constexpr (R == 2) {
+    const V a0 = u[0];
+    u[0] = cadd(a0, u[1]);
+    u[1] = csub(a0, u[1]);
+  } else if constexpr (R == 4) {
+    dft4(u[0], u[1], u[2], u[3], sd);
+  } else {
+    dft8(u, sd);
+  }
+}
+
+// The padded layout between the passes of a transform: element e sits at e + e / 16, which spreads
+// the strided writes of the early passes over the LDS banks. Where the padding of a sum is the sum
+// of the paddings, an access is one base per thread and a stride per pass (uniform, so it costs an
+// add; written element by element the shifts and adds were a quarter of all instructions of the
+// ring kernels, which the batched FP32 ones are bound by: VALU busy 80 to 100 %):
+//   inputs  j + r nb: nb = L / R a multiple of 16 (transforms of powers of two are padded from
+//           PAD_MIN points on, which makes it one; mixed-radix lengths are addressed one by one)
+//   outputs idx + r Ns, idx = (j - k) R + k: Ns a power of two; below 16, idx and r Ns never carry
+//           past a multiple of 16 (idx mod 16 < Ns modulo the steps of R Ns).
+constexpr int PAD_MIN = 128;
+__device__ __forceinline__ int padded_at(int e, bool pad) { return pad ? e + (e >> 4) : e; }
+
 // One radix-R pass (R = 2, 4 or 8) of an in-place Stockham FFT of length L in LDS,
 // after Ns points have been combined: butterfly j (j < L / R, k = j mod Ns) takes
 // input r < R from element j + r L / R, multiplies it by w^r with w = exp(dir 2 pi i
 // k / (R Ns)), takes its radix-R DFT and writes output r to element (j - k) R + k +
 // r Ns. NBF butterflies per thread; all inputs are read into registers before the
 // barrier that precedes the writes, so one buffer suffices and the layout may change
-// from pass to pass: element e sits at e (plain) or at fft_padded-style e + e / 16
-// (pad_in / pad_out), the padding that spreads the strided writes of the early
-// passes over the LDS banks. wk[k] = exp(-2 pi i k / (R Ns)), k < Ns: this pass's
-// twiddles, read by consecutive lanes at consecutive entries; the other powers are
-// products of it (at most three deep).
-template <class C, int NT, int R, int NBF>
+// from pass to pass: plain or padded (pad_in / pad_out). MIXED: L is not a power of two.
+// wk[k] = exp(-2 pi i k / (R Ns)), k < Ns: this pass's twiddles, read by consecutive lanes at
+// consecutive entries; the other powers are products of it (at most three deep).
+template <class C, int NT, int R, int NBF, bool MIXED = false>
 __device__ __forceinline__ void stockham_pass(typename CT<C>::V* x, int L, int Ns, int dir, bool pad_in,
                                               bool pad_out, const typename CT<C>::V* __restrict__ wk) {
   using V = typename CT<C>::V;
   const int tid = threadIdx.x;
   const C sd = (C)dir;
   const int nb = L / R;
-  auto at = [](int e, bool pad) { return pad ? e + (e >> 4) : e; };
+  const int si = padded_at(nb, pad_in);
   V v[R * NBF];
 #pragma unroll
   for (int b = 0; b < NBF; ++b) {
     const int j = tid + b * NT;
     if (j < nb) {
+      const int j0 = padded_at(j, pad_in);
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[R * b + r] = x[at(j + r * nb, pad_in)];
+      for (int r = 0; r < R; ++r) v[R * b + r] = MIXED ? x[padded_at(j + r * nb, pad_in)] : x[j0 + r * si];
     }
   }
   __syncthreads();
@@ -254,35 +296,11 @@ __device__ __forceinline__ void stockham_pass(typename CT<C>::V* x, int L, int N
     if (j < nb) {
       const int k = j & (Ns - 1);
       V* u = v + R * b;
-      if (Ns > 1) {
-        V w = wk[k];
-        if (dir > 0) w.y = -w.y;
-        u[1] = cmul(u[1], w);
-        if (R >= 4) {
-          const V w2 = cmul(w, w), w3 = cmul(w, w2);
-          u[2] = cmul(u[2], w2);
-          u[3] = cmul(u[3], w3);
-          if (R == 8) {
-            const V w4 = cmul(w2, w2);
-            u[4] = cmul(u[4], w4);
-            u[5] = cmul(u[5], cmul(w, w4));
-            u[6] = cmul(u[6], cmul(w2, w4));
-            u[7] = cmul(u[7], cmul(w3, w4));
-          }
-        }
-      }
-      if (R == 2) {
-        const V a0 = u[0];
-        u[0] = cadd(a0, u[1]);
-        u[1] = csub(a0, u[1]);
-      } else if (R == 4) {
-        dft4(u[0], u[1], u[2], u[3], sd);
-      } else {
-        dft8(u, sd);
-      }
-      const int idx = (j - k) * R + k;
+      if (Ns > 1) twiddle<R>(u, wk[k], dir);
+      butterfly<R>(u, sd);
+      const int i0 = padded_at((j - k) * R + k, pad_out);
 #pragma unroll
-      for (int r = 0; r < R; ++r) x[at(idx + r * Ns, pad_out)] = u[r];
+      for (int r = 0; r < R; ++r) x[i0 + padded_at(r * Ns, pad_out)] = u[r];
     }
   }
   __syncthreads();
@@ -303,7 +321,8 @@ __device__ __forceinline__ void fft_pow2(typename CT<C>::V* x, int lg, int dir,
   const int L = 1 << lg;
   int n2, n4, n8;
   fft_schedule(lg, &n2, &n4, &n8);
-  const int last = n2 + n4 + n8 - 1;
+  const int last = L < PAD_MIN ? 0 : n2 + n4 + n8 - 1;   // passes up to this one write the padded layout
+  const bool pad = L >= PAD_MIN;
   int Ns = 1, p = 0, off = 0;
   auto next = [&](int R) {
     off += Ns > 1 ? Ns : 0;
@@ -311,15 +330,15 @@ __device__ __forceinline__ void fft_pow2(typename CT<C>::V* x, int lg, int dir,
     ++p;
   };
   if (n2) {
-    stockham_pass<C, NT, 2, 2 * MAXB>(x, L, Ns, dir, p > 0, p < last, wt + off);
+    stockham_pass<C, NT, 2, 2 * MAXB>(x, L, Ns, dir, pad && p > 0, p < last, wt + off);
     next(2);
   }
   for (int q = 0; q < n4; ++q) {
-    stockham_pass<C, NT, 4, MAXB>(x, L, Ns, dir, p > 0, p < last, wt + off);
+    stockham_pass<C, NT, 4, MAXB>(x, L, Ns, dir, pad && p > 0, p < last, wt + off);
     next(4);
   }
   for (int q = 0; q < n8; ++q) {
-    stockham_pass<C, NT, 8, NB8>(x, L, Ns, dir, p > 0, p < last, wt + off);
+    stockham_pass<C, NT, 8, NB8>(x, L, Ns, dir, pad && p > 0, p < last, wt + off);
     next(8);
   }
 }
@@ -390,15 +409,15 @@ __device__ __forceinline__ void fft_mixed(typename CT<C>::V* x, int n, int mix, 
     ++p;
   };
   if (n2) {
-    stockham_pass<C, NT, 2, 2 * MAXB>(x, n, Ns, dir, p > 0, p < last, wt + off);
+    stockham_pass<C, NT, 2, 2 * MAXB, true>(x, n, Ns, dir, p > 0, p < last, wt + off);
     next(2);
   }
   for (int q = 0; q < n4; ++q) {
-    stockham_pass<C, NT, 4, MAXB>(x, n, Ns, dir, p > 0, p < last, wt + off);
+    stockham_pass<C, NT, 4, MAXB, true>(x, n, Ns, dir, p > 0, p < last, wt + off);
     next(4);
   }
   for (int q = 0; q < n8; ++q) {
-    stockham_pass<C, NT, 8, NB8>(x, n, Ns, dir, p > 0, p < last, wt + off);
+    stockham_pass<C, NT, 8, NB8, true>(x, n, Ns, dir, p > 0, p < last, wt + off);
     next(8);
   }
   for (int q = 0; q < n3; ++q) {
@@ -421,7 +440,8 @@ __device__ __forceinline__ void fft_mixed(typename CT<C>::V* x, int n, int mix, 
 // Plan-table index of entry e of the per-pass twiddle tables of a 2^lg-point
 // transform: for each pass with Ns > 1 (in pass order), entries off + k, k < Ns, hold
 // exp(-2 pi i k / (R Ns)) = glob[k glob_len / (R Ns)] of the plan's table glob[t] =
-// exp(-2 pi i t / glob_len), t < glob_len / 2.
+// exp(-2 pi i t / glob_len), t < glob_len / 2. Entries past them are those of a Bluestein ring's
+// inverse transform (passes 1 .. n2 + n4 of the radices 8, 2 and 4 ..., 8 ...).
 __device__ __forceinline__ int twiddle_glob_index(int lg, int e, int glob_len) {
   int n2, n4, n8;
   fft_schedule(lg, &n2, &n4, &n8);
@@ -434,76 +454,168 @@ __device__ __forceinline__ int twiddle_glob_index(int lg, int e, int glob_len) {
     }
     Ns *= R;
   }
+  Ns = 8;
+  for (int p = 0; p < n2 + n4; ++p) {
+    const int R = p < n2 ? 2 : 4;
+    if (e < off + Ns) return (e - off) * (glob_len / (R * Ns));
+    off += Ns;
+    Ns *= R;
+  }
   return 0;
 }
 
-// This thread's share of a ring's Bluestein chirp (cj[u] = chirp[tid + u NT], j < n)
-// and filter spectrum (hk[u] = H[tid + u NT], k < M), in registers.
-template <class C, int NT, int MAXB>
-struct BlueRegs {
-  static constexpr int NK = 4 * MAXB;     // M <= 4 MAXB NT
-  static constexpr int NJ = 2 * MAXB;     // n <= M / 2
-  typename CT<C>::V cj[NJ], hk[NK];
-  __device__ __forceinline__ void load(int n, int M, const typename CT<C>::V* __restrict__ chirp,
-                                       const typename CT<C>::V* __restrict__ H) {
-#pragma unroll
-    for (int u = 0; u < NJ; ++u) {
-      const int j = threadIdx.x + u * NT;
-      if (j < n) cj[u] = chirp[j];
-    }
-#pragma unroll
-    for (int u = 0; u < NK; ++u) {
-      const int k = threadIdx.x + u * NT;
-      if (k < M) hk[u] = H[k];
-    }
-  }
-};
+// One radix-R pass of a Bluestein convolution (see dft_bluestein), the butterflies, index map and
+// layouts of stockham_pass, with the products by the chirp and the filter in the registers of
+// the pass next to them:
+//   BL_FIRST  the inputs are the ring's n values (in natural order, conjugated for an inverse
+//             DFT) times the chirp, zero from n on: r < R / 2 only (n <= L / 2), none
+//             of the others read
+//   BL_MID    after the DFT (the forward transform's last pass, radix 8, whose outputs j + r L / 8
+//             are the inputs of butterfly j of a radix-8 first pass) the product with the filter
+//             spectrum H and that first pass of the inverse transform: one pass in LDS for both
+//   BL_LAST   the outputs, n of them, times the chirp / L (conjugated for an inverse DFT)
+//   BL_PLAIN  none of these
+enum BluePass { BL_PLAIN, BL_FIRST, BL_MID, BL_LAST };
 
-template <class C, int NT, int MAXB>
-__device__ void dft_bluestein(typename CT<C>::V* x, int n, int M, int lgM, int dir,
-                              const BlueRegs<C, NT, MAXB>& br,
-                              const typename CT<C>::V* __restrict__ wt) {
+template <class C, int NT, int R, int NBF, int KIND>
+__device__ __forceinline__ void blue_pass(typename CT<C>::V* x, int L, int Ns, int dir, bool pad_in, bool pad_out,
+                                          const typename CT<C>::V* __restrict__ wk, int n, bool inverse,
+                                          const typename CT<C>::V* __restrict__ tab) {
   using V = typename CT<C>::V;
-  constexpr int NK = BlueRegs<C, NT, MAXB>::NK;
-  constexpr int NJ = BlueRegs<C, NT, MAXB>::NJ;
   const int tid = threadIdx.x;
-  const V(&cj)[NJ] = br.cj;
-  const V(&hk)[NK] = br.hk;
+  const int nb = L / R;
+  const int si = padded_at(nb, pad_in);
+  // the chirp of the outputs / inputs, or the filter: entry j + r nb of the table for element r
+  constexpr int RT = KIND == BL_MID ? R : R / 2;
+  V t[KIND == BL_PLAIN ? 1 : RT * NBF];
+  if constexpr (KIND != BL_PLAIN) {
+    int here = 0;
+    asm volatile("" : "+s"(here));   // keeps the loads in this pass: earlier, they only hold registers
+    const int lim = KIND == BL_MID ? L : n;
 #pragma unroll
-  for (int u = 0; u < NK; ++u) {
-    const int j = tid + u * NT;
-    if (j < M) {
-      if (u < NJ && j < n) {
-        V v = x[j];
-        if (dir > 0) v = cconj(v);     // inverse DFT = conj(DFT(conj(x)))
-        x[j] = cmul(v, cj[u < NJ ? u : 0]);
-      } else {
-        x[j] = CT<C>::make(0, 0);
+    for (int b = 0; b < NBF; ++b)
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const int e = tid + b * NT + r * nb;
+        if (tid + b * NT < nb && e < lim) t[RT * b + r] = tab[e + here];
+      }
+  }
+  V v[R * NBF];
+#pragma unroll
+  for (int b = 0; b < NBF; ++b) {
+    const int j = tid + b * NT;
+    if (j < nb) {
+      const int j0 = padded_at(j, pad_in);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if constexpr (KIND == BL_FIRST) {
+          V y = CT<C>::make(0, 0);
+          if (r < R / 2 && j + r * nb < n) {
+            y = x[j + r * nb];
+            if (inverse) y = cconj(y);           // inverse DFT = conj(DFT(conj(x)))
+            y = cmul(y, t[RT * b + (r < RT ? r : 0)]);
+          }
+          v[R * b + r] = y;
+        } else {
+          v[R * b + r] = x[j0 + r * si];
+        }
       }
     }
   }
   __syncthreads();
-  fft_pow2<C, NT, MAXB>(x, lgM, -1, wt);
 #pragma unroll
-  for (int u = 0; u < NK; ++u) {
-    const int k = tid + u * NT;
-    if (k < M) x[k] = cmul(x[k], hk[u]);
-  }
-  __syncthreads();
-  fft_pow2<C, NT, MAXB>(x, lgM, +1, wt);
-  const C invM = (C)1 / (C)M;
+  for (int b = 0; b < NBF; ++b) {
+    const int j = tid + b * NT;
+    if (j < nb) {
+      V* u = v + R * b;
+      const int k = j & (Ns - 1);
+      if (Ns > 1) twiddle<R>(u, wk[k], dir);
+      butterfly<R>(u, (C)dir);
+      if constexpr (KIND == BL_MID) {
 #pragma unroll
-  for (int u = 0; u < NJ; ++u) {
-    const int k = tid + u * NT;
-    if (k < n) {
-      V v = cmul(x[k], cj[u]);
-      v.x *= invM;
-      v.y *= invM;
-      if (dir > 0) v = cconj(v);
-      x[k] = v;
+        for (int r = 0; r < R; ++r) u[r] = cmul(u[r], t[RT * b + r]);
+        butterfly<R>(u, (C)-dir);
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[padded_at(j * R, pad_out) + r] = u[r];
+      } else if constexpr (KIND == BL_LAST) {
+        const C inv = (C)1 / (C)L;
+#pragma unroll
+        for (int r = 0; r < R / 2; ++r)
+          if (j + r * nb < n) {
+            V y = cmul(u[r], t[RT * b + r]);
+            y.x *= inv;
+            y.y *= inv;
+            x[j + r * nb] = inverse ? cconj(y) : y;
+          }
+      } else {
+        const int i0 = padded_at((j - k) * R + k, pad_out);
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[i0 + padded_at(r * Ns, pad_out)] = u[r];
+      }
     }
   }
   __syncthreads();
+}
+
+template <class C, int NT, int MAXB, int KIND>
+__device__ __forceinline__ void blue_pass_r(int R, typename CT<C>::V* x, int L, int Ns, int dir, bool pad_in,
+                                            bool pad_out, const typename CT<C>::V* __restrict__ wk, int n, bool inverse,
+                                            const typename CT<C>::V* __restrict__ tab) {
+  constexpr int NB8 = (MAXB + 1) / 2;
+  if (R == 8)
+    blue_pass<C, NT, 8, NB8, KIND>(x, L, Ns, dir, pad_in, pad_out, wk, n, inverse, tab);
+  else if constexpr (KIND != BL_MID)   // R = 4: from 8 points on the schedule has no radix 2
+    blue_pass<C, NT, 4, MAXB, KIND>(x, L, Ns, dir, pad_in, pad_out, wk, n, inverse, tab);
+}
+
+// DFT of n points in place (natural order in and out, plain layout) by Bluestein's method: chirp,
+// forward transform of M = 2^lg >= 2 n - 1 points (radices as fft_schedule gives them, the last one
+// 8), product with the filter spectrum H, inverse transform, chirp. The inverse takes one
+// radix-8 pass first, then the smaller radices, then the other 8s, so that its first pass joins
+// the forward transform's last one in registers, and the chirps and the filter are applied
+// in the passes beside them: 2 P - 1 passes through LDS for P-pass transforms, where the products
+// apart took 2 P + 3 (M = 4096: 7 instead of 11, of two barriers each). The first pass does not read
+// the zero half of its inputs, the last one does not write the half that is not needed. The passes
+// are bound by LDS traffic and their barriers. At Nside 512: 64 maps FP32, the 4096-point
+// class 670 -> 643 us from this alone (520 with the waves of ring_waves and the order of ring_block);
+// FP64, one map: 40.0 -> 37.9 us together.
+// wt: per-pass twiddles of the forward transform (fft_twiddle_entries(lg)), then those of the
+// inverse's passes 1 .. n2 + n4, which differ (blue_twiddle_entries(lg)); its later passes share
+// the forward's.
+template <class C, int NT, int MAXB>
+__device__ __forceinline__ void dft_bluestein(typename CT<C>::V* x, int n, int lg, int dir, const typename CT<C>::V* __restrict__ chirp,
+                              const typename CT<C>::V* __restrict__ H, const typename CT<C>::V* __restrict__ wt) {
+  const int M = 1 << lg;
+  const bool inverse = dir > 0;
+  int n2, n4, n8;
+  fft_schedule(lg, &n2, &n4, &n8);
+  const int np = n2 + n4 + n8, small = n2 + n4;
+  auto radix = [&](int p) { return p < n2 ? 2 : (p < small ? 4 : 8); };
+  int Ns = 1, off = 0;
+  blue_pass_r<C, NT, MAXB, BL_FIRST>(radix(0), x, M, 1, -1, false, true, wt, n, inverse, chirp);
+  Ns = radix(0);
+  int p = 1;
+  for (; p < np - 1; ++p) {
+    blue_pass_r<C, NT, MAXB, BL_PLAIN>(radix(p), x, M, Ns, -1, true, true, wt + off, n, inverse, chirp);
+    off += Ns;
+    Ns *= radix(p);
+  }
+  blue_pass_r<C, NT, MAXB, BL_MID>(8, x, M, Ns, -1, true, true, wt + off, n, inverse, H);
+  // inverse: passes 1 .. np - 1 (radices 8, the small ones, 8 ...); offi: the forward table's offset of pass p
+  int ox = fft_twiddle_entries(lg), offi = 0, nf = 1;
+  Ns = 8;
+  for (p = 1; p < np; ++p) {
+    const int R = p <= small ? radix(p - 1) : 8;
+    offi += nf > 1 ? nf : 0;
+    nf *= radix(p - 1);
+    const typename CT<C>::V* w = p <= small ? wt + ox : wt + offi;
+    if (p < np - 1)
+      blue_pass_r<C, NT, MAXB, BL_PLAIN>(R, x, M, Ns, +1, true, true, w, n, inverse, chirp);
+    else
+      blue_pass_r<C, NT, MAXB, BL_LAST>(R, x, M, Ns, +1, true, false, w, n, inverse, chirp);
+    if (p <= small) ox += Ns;
+    Ns *= R;
+  }
 }
 
 // Plan tables in the FFT arithmetic type.
@@ -528,8 +640,6 @@ struct Tabs<float> {
 // per-pass twiddles of its power-of-two length (n, the 2^a of a mixed-radix length, or M)
 // staged in LDS (twl). KIND 0: the launch holds only power-of-two rings, 1: only rings
 // that are not (mixed radix and Bluestein, n at most half the class length), 2: any.
-// The Bluestein chirp and filter spectrum are loaded per transform (held across the
-// workgroup they cost occupancy).
 template <class C, int NT, int MAXB, int KIND>
 __device__ __forceinline__ void ring_dft(typename CT<C>::V* buf, const typename CT<C>::V* twl,
                                          const RingPair& rp, int dir, const PlanDev& P) {
@@ -539,9 +649,8 @@ __device__ __forceinline__ void ring_dft(typename CT<C>::V* buf, const typename 
     fft_mixed<C, NT, MAXB>(buf, rp.nphi, rp.mix, dir, twl, Tabs<C>::mix(P) + rp.bl_off);
   } else {
     if constexpr (KIND != 0) {
-      BlueRegs<C, NT, MAXB> br;
-      br.load(rp.nphi, rp.bl_M, Tabs<C>::chirp(P) + rp.chirp_off, Tabs<C>::blue(P) + rp.bl_off);
-      dft_bluestein<C, NT, MAXB>(buf, rp.nphi, rp.bl_M, __ffs(rp.bl_M) - 1, dir, br, twl);
+      dft_bluestein<C, NT, MAXB>(buf, rp.nphi, __ffs(rp.bl_M) - 1, dir, Tabs<C>::chirp(P) + rp.chirp_off,
+                                 Tabs<C>::blue(P) + rp.bl_off, twl);
     }
   }
 }
@@ -579,8 +688,8 @@ __device__ __forceinline__ RingPhase ring_phase(const RingPair& rp) {
     r.ph0 = make_double2(1.0, 0.0);
     r.step = r.ph0;
   } else {
-    r.ph0 = expipi<double>((int64_t)threadIdx.x * rp.ph_num, rp.nphi);
-    r.step = expipi<double>((int64_t)NT * rp.ph_num, rp.nphi);
+    r.ph0 = expipi<double>(threadIdx.x * rp.ph_num, rp.nphi);
+    r.step = expipi<double>(NT * rp.ph_num, rp.nphi);
   }
   return r;
 }
@@ -671,7 +780,7 @@ __device__ __forceinline__ void fold_synthesis(const PlanDev& P, const T* __rest
     V* part = reinterpret_cast<V*>(lds_raw);    // [np][N, S]
     for (int p = tid; p < np; p += NT) {
       const int k = p % n, g = p / n;
-      const double2 phd = rp.ph_num ? expipi<double>((int64_t)k, n) : make_double2(1.0, 0.0);   // exp(i k phi0)
+      const double2 phd = rp.ph_num ? expipi<double>(k, n) : make_double2(1.0, 0.0);   // exp(i k phi0)
       const V phk = CT<C>::make((C)phd.x, (C)phd.y);
       V bn = CT<C>::make(0, 0), bs = CT<C>::make(0, 0);
       C sg = (g & 1) ? sig : (C)1;                  // sig^t, t = g + u G
@@ -804,7 +913,7 @@ __device__ __forceinline__ void phase_b_body(const PlanDev& P, const PhaseBArgs&
   constexpr int TWP = (2 * MAXB + 2) / 3;
   static_assert(TWP <= 3, "twiddle prefetch holds at most three entries per thread");
   const int tw_lg = ring_twiddle_lg(rp);
-  const int tw_n = fft_twiddle_entries(tw_lg);
+  const int tw_n = fft_twiddle_entries(tw_lg) + (rp.bl_M > 0 ? blue_twiddle_entries(tw_lg) : 0);
   const V* __restrict__ twg = Tabs<C>::tw(P);
   auto tw_load = [&](int e) { return e < tw_n ? twg[twiddle_glob_index(tw_lg, e, P.tw_len)] : CT<C>::make(0, 0); };
   const V tw0 = tw_load(tid);
@@ -951,7 +1060,7 @@ __device__ __forceinline__ void phase_b_pol_body(const PlanDev& P, const PolRing
 
   V* twl = buf + fft_padded(buf_elems);
   const int tw_lg = ring_twiddle_lg(rp);
-  const int tw_n = fft_twiddle_entries(tw_lg);
+  const int tw_n = fft_twiddle_entries(tw_lg) + (rp.bl_M > 0 ? blue_twiddle_entries(tw_lg) : 0);
   const V* __restrict__ twg = Tabs<C>::tw(P);
   auto stage_twiddles = [&]() {
     for (int e = tid; e < tw_n; e += NT) twl[e] = twg[twiddle_glob_index(tw_lg, e, P.tw_len)];
@@ -1042,23 +1151,51 @@ __device__ __forceinline__ void phase_b_pol_body(const PlanDev& P, const PolRing
   }
 }
 
+// Block b of a ring launch: the entry of the ring list and the map. Workgroups go to the eight XCDs
+// in turn; every eighth block is the next map of one ring pair, so all maps of a ring pair run on
+// one XCD close together and its tables (chirp, filter, twiddles) and tau N^-1 come from that L2.
+// (All ring pairs of a map in turn, 64 FP32 maps at Nside 512 fetched the 45 KB of tables of a
+// 4096-point ring once per map: 1.35 GB for 0.43 GB of data. Groups of four neighbouring ring
+// pairs per map instead of one: 8 % slower.)
+struct RingBlock {
+  int ring, map;
+};
+__device__ __forceinline__ RingBlock ring_block(unsigned b, int nmaps) {
+  if (nmaps == 1) return {(int)b, 0};
+  const unsigned t = b >> 3, g = t / (unsigned)nmaps;
+  return {(int)(g * 8 + (b & 7)), (int)(t - g * nmaps)};
+}
+
 template <int NT, int MAXB, int CLS>
 __global__ void __launch_bounds__(NT) phase_b_pol_kernel(PlanDev P, PolRingArgs a, const int32_t* __restrict__ qlist,
-                                                          int buf_elems) {
-  phase_b_pol_body<double, NT, MAXB, class_kind(CLS)>(P, a, qlist[blockIdx.x], blockIdx.y, buf_elems);
+                                                          int count, int buf_elems) {
+  const RingBlock rb = ring_block(blockIdx.x, a.nmaps);
+  if (rb.ring < count) phase_b_pol_body<double, NT, MAXB, class_kind(CLS)>(P, a, qlist[rb.ring], rb.map, buf_elems);
+}
+
+// Waves per SIMD that the registers of a ring kernel have to leave room for (1: no constraint). A
+// workgroup of 512 threads takes two of a SIMD's waves at once, so its registers decide between
+// one, two and three workgroups a CU: FP64 up to 4096 points at four (123 registers; 47 -> 37 us for
+// one map at Nside 512), FP32 at six (80 registers; 64 maps: 643 -> 520 us; the shorter
+// class of few maps 304 us at five, 244 at six). 8192 points need more registers than that, and
+// the power-of-two and one-wave kernels ran slower under a limit.
+template <class C>
+constexpr int ring_waves(int nt, int cls, int maxb) {
+  if (cls != 0) return 1;
+  return sizeof(C) == 4 ? (maxb == 4 ? 1 : 6) : (maxb == 4 ? 1 : 4);
 }
 
 template <class T, class C, int NT, int MAXB, int CLS>
-__global__ void __launch_bounds__(NT) phase_b_kernel(PlanDev P, PhaseBArgs a, const int32_t* __restrict__ qlist,
-                                                     int buf_elems) {
-  phase_b_body<T, C, NT, MAXB, class_kind(CLS)>(P, a, qlist[blockIdx.x], blockIdx.y, buf_elems);
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ring_waves<C>(NT, CLS, MAXB)))) phase_b_kernel(PlanDev P, PhaseBArgs a, const int32_t* __restrict__ qlist,
+                                                     int count, int buf_elems) {
+  const RingBlock rb = ring_block(blockIdx.x, a.nmaps);
+  if (rb.ring < count) phase_b_body<T, C, NT, MAXB, class_kind(CLS)>(P, a, qlist[rb.ring], rb.map, buf_elems);
 }
 
-// Task groups (float storage and arithmetic): block b of task t covers entry
-// (b - offs[t]) / nmaps of the task's ring-pair list of class CLS and map
-// (b - offs[t]) % nmaps.
+// Task groups (float storage and arithmetic): the blocks of task t cover its ring-pair list of
+// class CLS and its maps as a launch of its own would (ring_block).
 template <int NT, int CLS, int MAXB>
-__global__ void __launch_bounds__(NT) group_phase_b_kernel(GroupArgs g, int buf_elems) {
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ring_waves<float>(NT, CLS, MAXB)))) group_phase_b_kernel(GroupArgs g, int buf_elems) {
   const int lo = group_task_of(g, blockIdx.x);
   const TaskDev& t = g.t[lo];
   const int64_t local = blockIdx.x - g.offs[lo];
@@ -1073,8 +1210,9 @@ __global__ void __launch_bounds__(NT) group_phase_b_kernel(GroupArgs g, int buf_
   a.map_out = t.map_out;
   a.slots = t.slots;
   a.q_stride = t.q_stride;
-  phase_b_body<float, float, NT, MAXB, class_kind(CLS)>(t.P, a, t.ring_q[CLS][local / t.nmaps],
-                                                        (int)(local % t.nmaps), buf_elems);
+  const RingBlock rb = ring_block((unsigned)local, t.nmaps);
+  if (rb.ring < t.ring_n[CLS])
+    phase_b_body<float, float, NT, MAXB, class_kind(CLS)>(t.P, a, t.ring_q[CLS][rb.ring], rb.map, buf_elems);
 }
 
 // Threads of a ring workgroup per launch class: Bluestein rings 512, power-of-two
@@ -1093,8 +1231,8 @@ template <class T, class C, int NT, int MAXB, int CLS>
 hipError_t launch_class_b(const PlanDev& P, const PhaseBArgs& a, const RingClass& rc, hipStream_t s) {
   const size_t lds = ring_lds_bytes(rc.fft_len, sizeof(typename CT<C>::V));
   if (hipError_t e = ensure_dynamic_lds((const void*)phase_b_kernel<T, C, NT, MAXB, CLS>, lds)) return e;
-  hipLaunchKernelGGL((phase_b_kernel<T, C, NT, MAXB, CLS>), dim3(rc.count, a.nmaps), dim3(NT), lds, s, P, a, rc.q,
-                     rc.fft_len);
+  hipLaunchKernelGGL((phase_b_kernel<T, C, NT, MAXB, CLS>), dim3(ring_blocks(rc.count, a.nmaps)), dim3(NT), lds, s, P, a, rc.q,
+                     rc.count, rc.fft_len);
   return hipGetLastError();
 }
 
@@ -1102,6 +1240,13 @@ template <class T, class C, int CLS>
 hipError_t launch_class(const PlanDev& P, const PhaseBArgs& a, const RingClass& rc, hipStream_t s) {
   if (rc.count == 0) return hipSuccess;
   constexpr int NT = ring_threads(CLS);
+  // Batched, transforms of up to 2048 points take 256 threads as the power-of-two rings do: in 512
+  // half of them idle in the radix-8 passes. (One map fills the chip with neither; there the
+  // fold, update and unfold of a ring are shorter on 512.)
+  if constexpr (CLS == 0)
+    if (a.nmaps >= RING_SPLIT_MAPS && rc.fft_len <= 2048)
+      return rc.fft_len <= 1024 ? launch_class_b<T, C, 256, 1, CLS>(P, a, rc, s)
+                                : launch_class_b<T, C, 256, 2, CLS>(P, a, rc, s);
   switch (maxb_for(rc.fft_len, NT)) {
     case 1: return launch_class_b<T, C, NT, 1, CLS>(P, a, rc, s);
     case 2: return launch_class_b<T, C, NT, 2, CLS>(P, a, rc, s);
@@ -1142,8 +1287,8 @@ template <int NT, int MAXB, int CLS>
 hipError_t launch_pol_class_b(const PlanDev& P, const PolRingArgs& a, const RingClass& rc, hipStream_t s) {
   const size_t lds = ring_lds_bytes(rc.fft_len, sizeof(double2));
   if (hipError_t e = ensure_dynamic_lds((const void*)phase_b_pol_kernel<NT, MAXB, CLS>, lds)) return e;
-  hipLaunchKernelGGL((phase_b_pol_kernel<NT, MAXB, CLS>), dim3(rc.count, a.nmaps), dim3(NT), lds, s, P, a, rc.q,
-                     rc.fft_len);
+  hipLaunchKernelGGL((phase_b_pol_kernel<NT, MAXB, CLS>), dim3(ring_blocks(rc.count, a.nmaps)), dim3(NT), lds, s, P, a, rc.q,
+                     rc.count, rc.fft_len);
   return hipGetLastError();
 }
 
