@@ -267,12 +267,16 @@ int run_phase_b(wf_plan_s* p, hipStream_t s, int mode, int nmaps, double lam, co
   a.map_in = map_in;
   a.map_out = map_out;
   const Geometry& g = *p->geo;
-  // With few maps, one launch per transform kind fills the GPU better than also
+  const bool fp32 = p->dtype != WF_F64;
+  if (g.one_ring_launch(nmaps)) {
+    TIMED(0, MWF_HIP(launch_phase_b_all(p->dev, a, g.ring_all, fp32, s)));
+    return WF_OK;
+  }
+  // With few maps at the largest Nside, one launch per transform kind fills the GPU better than also
   // splitting off the short transforms; the two kinds then run side by side (the
   // Bluestein class on the plan's second stream), since neither alone fills it
   const int split = nmaps >= RING_SPLIT_MAPS ? 1 : 0;
   const RingClass* cls = g.ring_cls[split];
-  const bool fp32 = p->dtype != WF_F64;
   if (split) {
     // the rings of the longest transforms, the other long ones that are not a power of two
     // at their own lengths, the long power-of-two rings, the short ones one wave per pair
@@ -282,10 +286,6 @@ int run_phase_b(wf_plan_s* p, hipStream_t s, int mode, int nmaps, double lam, co
       MWF_HIP(launch_phase_b_class(p->dev, a, cls[1], 1, fp32, s));
       MWF_HIP(launch_phase_b_class(p->dev, a, cls[2], 2, fp32, s));
     });
-    return WF_OK;
-  }
-  if (cls[0].count == 0 || cls[1].count == 0) {
-    TIMED(0, MWF_HIP(launch_phase_b(p->dev, a, cls, fp32, s)));
     return WF_OK;
   }
   if (int rc = ensure_aux(p)) return rc;

@@ -313,6 +313,24 @@ int build_geometry(Geometry& g) {
       if ((rc = M.upload(&d, bl[k]))) return rc;
       g.blue_split[k] = RingClass{d, (int32_t)bl[k].size(), bl_len[k]};
     }
+    // All ring pairs in one list, longest transforms first, up to Nside 512 (at 1024 the FP64 buffer
+    // of the longest leaves one workgroup a CU, and the other rings would take its size): one or a
+    // few maps take one launch. The launches by kind, the event pair that forked and joined their
+    // streams and the gaps around them were half of a sweep at Nside 16 to 64.
+    if (std::max(lens[0][0], lens[0][1]) <= RING_ONE_LAUNCH) {
+      std::vector<int32_t> all(g.npairs);
+      for (int q = 0; q < g.npairs; ++q) all[q] = q;
+      auto own_len = [&](int q) { return pairs[q].mix ? pairs[q].nphi : class_len(pairs[q]); };
+      std::stable_sort(all.begin(), all.end(), [&](int a, int b) {
+        auto cost = [&](int q) { return (pairs[q].bl_M > 0 ? 2 : 1) * own_len(q); };
+        return cost(a) > cost(b);
+      });
+      int len = 4;
+      for (int q : all) len = std::max(len, own_len(q));
+      int32_t* d = nullptr;
+      if ((rc = M.upload(&d, all))) return rc;
+      g.ring_all = RingClass{d, g.npairs, len};
+    }
     // the same split of the batched class 0: at 64 maps the 2048-point Bluestein rings and
     // the long mixed-radix rings ran in the launch sized for the 4096-point ones
     std::vector<int32_t> ls[2];

@@ -293,6 +293,7 @@ inline int64_t ring_blocks(int count, int nmaps) {
 // 512 threads) and class 1 power-of-two rings (256 threads), class 2 transforms of at
 // most 1024 points (one wave per ring pair; used from RING_SPLIT_MAPS maps on, when
 // classes 0 and 1 hold only the longer transforms).
+constexpr int RING_ONE_LAUNCH = 4096;   // longest transform of a geometry whose ring pairs go in one launch
 constexpr int NRING_CLASSES = 3;
 constexpr int RING_SPLIT_MAPS = 4;
 
@@ -355,6 +356,9 @@ inline size_t ring_lds_bytes(int fft_len, size_t elem) {
 // Zero `bytes` (a multiple of 16, 16-byte aligned) at p on s with a kernel.
 hipError_t launch_zero_fill(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_phase_b(const PlanDev& P, const PhaseBArgs& a, const RingClass* cls, bool fp32, hipStream_t s);
+// Every ring pair in one launch, transforms of any kind up to RING_ONE_LAUNCH points: 256 threads a pair up
+// to 2048 points, 512 above.
+hipError_t launch_phase_b_all(const PlanDev& P, const PhaseBArgs& a, const RingClass& rc, bool fp32, hipStream_t s);
 // One class alone (cls: its index, which fixes the workgroup size).
 hipError_t launch_phase_b_class(const PlanDev& P, const PhaseBArgs& a, const RingClass& rc, int cls, bool fp32,
                                 hipStream_t s);
@@ -530,7 +534,8 @@ struct PolRingArgs {
   double* map_out;
   const double* q6;
 };
-// The ring launch classes 0 and 1 of a polarised plan (512 threads).
+// The ring launch classes 0 and 1 of a polarised plan (512 threads). One launch for both needs more
+// registers than it has (256 and 17 spilled; three sweeps at Nside 512: 4140 -> 4370 us).
 hipError_t launch_pol_ring(const PlanDev& P, const PolRingArgs& a, const RingClass* cls, hipStream_t s);
 
 // Spin-2 Legendre tables and work of a polarised plan (FP64). The functions

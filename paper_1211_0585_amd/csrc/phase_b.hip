@@ -1181,13 +1181,13 @@ __global__ void __launch_bounds__(NT) phase_b_pol_kernel(PlanDev P, PolRingArgs 
 // the power-of-two and one-wave kernels ran slower under a limit.
 template <class C>
 constexpr int ring_waves(int nt, int cls, int maxb) {
-  if (cls != 0) return 1;
+  if (nt != 512 && cls != 0) return 1;
   return sizeof(C) == 4 ? (maxb == 4 ? 1 : 6) : (maxb == 4 ? 1 : 4);
 }
 
 template <class T, class C, int NT, int MAXB, int CLS>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ring_waves<C>(NT, CLS, MAXB)))) phase_b_kernel(PlanDev P, PhaseBArgs a, const int32_t* __restrict__ qlist,
-                                                     int count, int buf_elems) {
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ring_waves<C>(NT, CLS, MAXB))))
+phase_b_kernel(PlanDev P, PhaseBArgs a, const int32_t* __restrict__ qlist, int count, int buf_elems) {
   const RingBlock rb = ring_block(blockIdx.x, a.nmaps);
   if (rb.ring < count) phase_b_body<T, C, NT, MAXB, class_kind(CLS)>(P, a, qlist[rb.ring], rb.map, buf_elems);
 }
@@ -1256,6 +1256,13 @@ hipError_t launch_class(const PlanDev& P, const PhaseBArgs& a, const RingClass& 
 }
 
 template <class T, class C>
+hipError_t launch_all(const PlanDev& P, const PhaseBArgs& a, const RingClass& rc, hipStream_t s) {
+  static_assert(RING_ONE_LAUNCH <= 4096, "two radix-4 butterflies each of 512 threads");
+  if (rc.fft_len > 2048) return launch_class_b<T, C, 512, 2, 2>(P, a, rc, s);
+  return rc.fft_len <= 1024 ? launch_class_b<T, C, 256, 1, 2>(P, a, rc, s) : launch_class_b<T, C, 256, 2, 2>(P, a, rc, s);
+}
+
+template <class T, class C>
 hipError_t launch_t(const PlanDev& P, const PhaseBArgs& a, const RingClass* cls, hipStream_t s) {
   hipError_t e = launch_class<T, C, 0>(P, a, cls[0], s);
   if (e == hipSuccess) e = launch_class<T, C, 1>(P, a, cls[1], s);
@@ -1316,6 +1323,10 @@ hipError_t launch_group_phase_b(const GroupLaunch& g, int cls, int fft_len, hipS
 
 hipError_t launch_phase_b(const PlanDev& P, const PhaseBArgs& a, const RingClass* cls, bool fp32, hipStream_t s) {
   return fp32 ? launch_t<float, float>(P, a, cls, s) : launch_t<double, double>(P, a, cls, s);
+}
+
+hipError_t launch_phase_b_all(const PlanDev& P, const PhaseBArgs& a, const RingClass& rc, bool fp32, hipStream_t s) {
+  return fp32 ? launch_all<float, float>(P, a, rc, s) : launch_all<double, double>(P, a, rc, s);
 }
 
 hipError_t launch_phase_b_class(const PlanDev& P, const PhaseBArgs& a, const RingClass& rc, int cls, bool fp32,

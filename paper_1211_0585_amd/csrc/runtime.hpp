@@ -101,6 +101,15 @@ struct Geometry {
   // few-maps plan launches: the Bluestein rings split by transform length, [0] those
   // of the longest M, [1] the rest (each launch's LDS sized to its own length)
   RingClass blue_split[2]{};
+  // every ring pair, for one launch (count 0: the longest transform is over RING_ONE_LAUNCH points)
+  RingClass ring_all{};
+  // One launch or one per class. One map: a sweep at Nside 16, 64, 128, 256 and 512 took 52, 54, 66, 96 and
+  // 250 us in launches by kind and takes 27, 32, 45, 76 and 244 us in one. 8 maps, FP64: 29, 50,
+  // 109, 417 and 1726 against 28, 47, 102, 363 and 1729 us. Beyond, the short rings' one-wave launch wins (64 maps
+  // at Nside 64: 128 against 169 us; 16 at Nside 512, FP32: 1423 against 1452), except where the longest
+  // transform is one of 2048 points, whose 256 threads suit nearly every ring: Nside 256, FP32, 16 maps
+  // 318 against 289 us, 24 maps 513 against 492, 64 maps 1124 against 1135.
+  bool one_ring_launch(int nmaps) const { return ring_all.count && nmaps <= (ring_all.fft_len == 2048 ? 24 : 8); }
   // the batched class 0 (rings that are not a power of two, longer than SMALL_FFT) split the
   // same way for a plan's own launches: [0] the longest transforms, [1] the others at their
   // own lengths (mixed radix at n, not 2 n)

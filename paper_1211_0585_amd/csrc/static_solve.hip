@@ -120,7 +120,10 @@ extern "C" int wf_solve_batch_static(wf_plan_t p, int32_t nmaps, const void* d, 
     a.G = G;
     a.d = dd;
     a.map_out = out;
-    MWF_HIP(launch_phase_b(P, a, cls, !fp64, s));
+    if (g.one_ring_launch(nmaps))
+      MWF_HIP(launch_phase_b_all(P, a, g.ring_all, !fp64, s));
+    else
+      MWF_HIP(launch_phase_b(P, a, cls, !fp64, s));
     return WF_OK;
   };
   MfmaArgs ma{};
