@@ -23,11 +23,12 @@
 // Both spins of a ring share one scale: they are rescaled together once per chunk, and
 // while the scale is positive the ring contributes nothing (as for spin 0).
 //
-// Work: one workgroup of four waves per (m, block of 256 ring pairs); each wave owns 64
-// ring pairs, one per lane. The analysis reduces each chunk of 8 values of l over the
-// lanes (halves folded in registers, then LDS) and over the four waves (LDS), and
-// writes one partial sum of (E, B) per (l, m, block). The synthesis needs no
-// reduction and writes F_Q, F_U of its ring pairs.
+// Work: one workgroup per (m, block of 256 ring pairs). The analysis takes two waves with two
+// ring pairs per lane, reduces each chunk of 8 values of l over the lanes (quarters folded in
+// registers, then LDS) and over the waves (LDS), and writes one partial sum of (E, B) per
+// (l, m, block). The synthesis takes four waves with one ring pair per lane; it needs no reduction
+// and writes F_Q, F_U of its ring pairs. A wave of the analysis whose rings are all still scaled
+// runs the recurrence alone (in the synthesis that second loop costs a wave per SIMD: 290 -> 310 us).
 #include "mwf_internal.hpp"
 
 namespace mwf {
@@ -35,7 +36,9 @@ namespace {
 
 constexpr double BIG_THRESH = 0x1p64;
 constexpr double RESCALE = 0x1p-512;
-constexpr int S2_WAVES = 4;
+constexpr int S2_WAVES = 4;    // synthesis: one ring pair per lane
+constexpr int S2_AWAVES = 2;   // analysis: two ring pairs per lane
+static_assert(S2_WAVES == 2 * S2_AWAVES, "both take a work item's 256 ring pairs");
 constexpr int S2_TILE = 64;   // values of l per prefetched coefficient tile
 constexpr int S2_ACH = 8;     // values of l per reduction and scale check
 constexpr int S2_NV = 4 * S2_ACH;   // reduced values per chunk: (E re, E im, B re, B im) per l
@@ -48,6 +51,16 @@ __device__ __forceinline__ double fold_halves(double a, double b) {
   const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false,
                                                    false);
   const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false,
+                                                   false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+// Lanes 0-15 and 32-47: a over rows 0 + 1 and 2 + 3 of 16 lanes; lanes 16-31 and 48-63: b likewise
+// (v_permlane16_swap exchanges the odd rows of a with the even rows of b).
+__device__ __forceinline__ double fold_rows(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false,
+                                                   false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false,
                                                    false);
   return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
 }
@@ -85,6 +98,16 @@ __device__ __forceinline__ void s2_init(const PlanDev& P, const Spin2Dev& S2, in
     r.op = c * 0.5 * (1.0 - z);                      // l = 2 is the odd register for m = 1
     r.om = -(c * 0.5 * (1.0 + z));
   }
+}
+
+// Steps of l - m even and odd, both spins.
+__device__ __forceinline__ void s2_even(S2Ring& r, double A, double B) {
+  r.ep = fma(fma(A, r.z, B), r.op, -r.ep);
+  r.em = fma(fma(A, r.z, -B), r.om, -r.em);
+}
+__device__ __forceinline__ void s2_odd(S2Ring& r, double A, double B) {
+  r.op = fma(fma(A, r.z, B), r.ep, -r.op);
+  r.om = fma(fma(A, r.z, -B), r.em, -r.om);
 }
 
 // Once per chunk: bring large scaled values back by 2^-512 (both spins). Returns 1 if
@@ -127,38 +150,46 @@ __device__ __forceinline__ void s2_inputs(const double4& gq, const double4& gu, 
   in.o[6] = -DUr + SQi; in.o[7] = -DUi - SQr;
 }
 
-__global__ void __launch_bounds__(S2_WAVES * LANES) spin2_analysis_kernel(PlanDev P, Spin2Dev S2,
+// Bound by FP64 issue: 12 multiply-adds per l and ring pair, and the sum over the lanes, which costs the
+// same for any number of ring pairs per lane (two halve its share). The four sums of an l are
+// folded to one register as soon as they are formed, so no chunk of accumulators is live. At Nside 512,
+// lmax 1024, one map: 590 -> 397 us (one ring pair per lane and 32 live sums before; held to the
+// registers of four waves per SIMD, with 4 spilled, 424 us).
+__global__ void __launch_bounds__(S2_AWAVES * LANES) spin2_analysis_kernel(PlanDev P, Spin2Dev S2,
                                                                           const double* __restrict__ G,
                                                                           double* __restrict__ partial, int nblk2) {
-  __shared__ double red_w[S2_WAVES][S2_NV][LANES / 2 + 1];
-  __shared__ double sA_w[S2_WAVES][S2_TILE], sB_w[S2_WAVES][S2_TILE];
-  __shared__ double wsum[2][S2_WAVES][S2_NV];
+  __shared__ double red_w[S2_AWAVES][S2_NV][16 + 1];
+  __shared__ double sA_w[S2_AWAVES][S2_TILE], sB_w[S2_AWAVES][S2_TILE];
+  __shared__ double wsum[2][S2_AWAVES][S2_NV];
   const int wave = threadIdx.x / LANES, lane = threadIdx.x % LANES;
   const WorkItem it = S2.items[blockIdx.x];
   const int map = blockIdx.y;
   const int m = it.m, blk = it.blk;
   const int lmax = P.lmax;
   const int nact = P.n_active[m];
-  const int q = blk * (S2_WAVES * LANES) + wave * LANES + lane;
-  const bool valid = q < nact;
-  double(*red)[LANES / 2 + 1] = red_w[wave];
+  const int q0 = (blk * S2_AWAVES + wave) * (2 * LANES) + lane;
+  double(*red)[16 + 1] = red_w[wave];
   double* sA = sA_w[wave];
   double* sB = sB_w[wave];
   const size_t pstride = gf_stride(lmax);
   const double* Gq = G + (((size_t)1 * S2.field_maps + map) * P.npairs) * pstride + (size_t)m * 4;
   const double* Gu = G + (((size_t)2 * S2.field_maps + map) * P.npairs) * pstride + (size_t)m * 4;
 
-  S2Ring r;
-  s2_init(P, S2, m, q, valid, r);
-  S2In in;
-  {
+  S2Ring ra, rb;   // ring pairs q0 and q0 + LANES
+  S2In ia, ib;
+  auto load = [&](int q, bool valid, bool on, S2In& in) {
     double4 gq = make_double4(0, 0, 0, 0), gu = gq;
     if (valid) {
       gq = *reinterpret_cast<const double4*>(Gq + (size_t)q * pstride);
       gu = *reinterpret_cast<const double4*>(Gu + (size_t)q * pstride);
     }
-    s2_inputs(gq, gu, valid && r.sc == 0, in);
-  }
+    s2_inputs(gq, gu, on, in);
+  };
+  const bool va = q0 < nact, vb = q0 + LANES < nact;
+  s2_init(P, S2, m, q0, va, ra);
+  s2_init(P, S2, m, q0 + LANES, vb, rb);
+  load(q0, va, va && ra.sc == 0, ia);
+  load(q0 + LANES, vb, vb && rb.sc == 0, ib);
   const int64_t roff = P.row_off[m];
   const double* __restrict__ Arow = S2.A + roff;
   const double* __restrict__ Brow = S2.B + roff;
@@ -174,67 +205,68 @@ __global__ void __launch_bounds__(S2_WAVES * LANES) spin2_analysis_kernel(PlanDe
   const int64_t row = alm_index(lmax, m, m);
   int par = 0;
 
+  // sums of one l over the lanes' ring pairs: rows of 16 lanes hold E re, B re, E im, B im
+  auto sums = [&](double pa, double na, const double (&xa)[8], double pb, double nb, const double (&xb)[8]) {
+    const double er = fma(pb, xb[0], fma(nb, xb[2], fma(pa, xa[0], na * xa[2])));
+    const double ei = fma(pb, xb[1], fma(nb, xb[3], fma(pa, xa[1], na * xa[3])));
+    const double br = fma(pb, xb[4], fma(nb, xb[6], fma(pa, xa[4], na * xa[6])));
+    const double bi = fma(pb, xb[5], fma(nb, xb[7], fma(pa, xa[5], na * xa[7])));
+    return fold_rows(fold_halves(er, ei), fold_halves(br, bi));
+  };
+
   for (int l0 = m; l0 <= lmax; l0 += S2_ACH) {
     const int t0 = (l0 - m) & (S2_TILE - 1);
     if (t0 == 0 && l0 > m) {
+      wave_sync();
       sA[lane] = An;
       sB[lane] = Bn;
       wave_sync();
       An = tile_a(l0 - m + S2_TILE + lane);
       Bn = tile_b(l0 - m + S2_TILE + lane);
     }
-    double acc[S2_NV];
-#pragma unroll
-    for (int i = 0; i < S2_NV; ++i) acc[i] = 0.0;
-#pragma unroll
-    for (int j = 0; j < S2_ACH; j += 2) {
-      {
-        const double A = sA[t0 + j], B = sB[t0 + j];
-        const double tp = fma(A, r.z, B), tm = fma(A, r.z, -B);
-        r.ep = fma(tp, r.op, -r.ep);
-        r.em = fma(tm, r.om, -r.em);
-        acc[4 * j + 0] = fma(r.ep, in.e[0], r.em * in.e[2]);
-        acc[4 * j + 1] = fma(r.ep, in.e[1], r.em * in.e[3]);
-        acc[4 * j + 2] = fma(r.ep, in.e[4], r.em * in.e[6]);
-        acc[4 * j + 3] = fma(r.ep, in.e[5], r.em * in.e[7]);
-      }
-      {
-        const double A = sA[t0 + j + 1], B = sB[t0 + j + 1];
-        const double tp = fma(A, r.z, B), tm = fma(A, r.z, -B);
-        r.op = fma(tp, r.ep, -r.op);
-        r.om = fma(tm, r.em, -r.om);
-        acc[4 * j + 4] = fma(r.op, in.o[0], r.om * in.o[2]);
-        acc[4 * j + 5] = fma(r.op, in.o[1], r.om * in.o[3]);
-        acc[4 * j + 6] = fma(r.op, in.o[4], r.om * in.o[6]);
-        acc[4 * j + 7] = fma(r.op, in.o[5], r.om * in.o[7]);
-      }
-    }
-    // over the lanes: values 0..15 folded into lanes 0..31, 16..31 into lanes 32..63,
-    // then two lanes per value add 16 entries each
-#pragma unroll
-    for (int i = 0; i < S2_NV / 2; ++i) red[i + (lane >> 5) * (S2_NV / 2)][lane & 31] = fold_halves(acc[i], acc[S2_NV / 2 + i]);
-    wave_sync();
     const int v = lane >> 1;
-    const int h = (lane & 1) * 16;
     double sum = 0.0;
+    // a lane's pair past the active ones counts as scaled: its inputs are zero
+    if (__all((ra.sc > 0 || !va) && (rb.sc > 0 || !vb))) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) sum += red[v][h + k];
-    sum += __shfl_xor(sum, 1);
+      for (int j = 0; j < S2_ACH; j += 2) {
+        const double A0 = sA[t0 + j], B0 = sB[t0 + j], A1 = sA[t0 + j + 1], B1 = sB[t0 + j + 1];
+        s2_even(ra, A0, B0);
+        s2_even(rb, A0, B0);
+        s2_odd(ra, A1, B1);
+        s2_odd(rb, A1, B1);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < S2_ACH; j += 2) {
+        const double A0 = sA[t0 + j], B0 = sB[t0 + j], A1 = sA[t0 + j + 1], B1 = sB[t0 + j + 1];
+        s2_even(ra, A0, B0);
+        s2_even(rb, A0, B0);
+        red[4 * j + (lane >> 4)][lane & 15] = sums(ra.ep, ra.em, ia.e, rb.ep, rb.em, ib.e);
+        s2_odd(ra, A1, B1);
+        s2_odd(rb, A1, B1);
+        red[4 * j + 4 + (lane >> 4)][lane & 15] = sums(ra.op, ra.om, ia.o, rb.op, rb.om, ib.o);
+      }
+      wave_sync();
+      // two lanes per value add 8 entries each
+      const double* e = &red[v][(lane & 1) * 8];
+      sum = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+      sum += __shfl_xor(sum, 1);
+    }
     // over the waves of the workgroup (two slots alternate, one barrier per chunk)
     if ((lane & 1) == 0) wsum[par][wave][v] = sum;
     __syncthreads();
     if (wave == 0 && lane < S2_NV) {
-      const double t = wsum[par][0][lane] + wsum[par][1][lane] + wsum[par][2][lane] + wsum[par][3][lane];
+      const double t = wsum[par][0][lane] + wsum[par][1][lane];
       const int l = l0 + (lane >> 2);
-      if (l <= lmax) out[(row + (l - m)) * 4 + (lane & 3)] = t;
+      // the rows' order (E re, B re, E im, B im) to (E re, E im, B re, B im)
+      if (l <= lmax) out[(row + (l - m)) * 4 + ((lane & 1) * 2 + ((lane >> 1) & 1))] = t;
     }
     par ^= 1;
     wave_sync();
-    if (__any(r.sc) && s2_rescale(r)) {
-      const double4 gq = *reinterpret_cast<const double4*>(Gq + (size_t)q * pstride);
-      const double4 gu = *reinterpret_cast<const double4*>(Gu + (size_t)q * pstride);
-      s2_inputs(gq, gu, true, in);
-      __builtin_amdgcn_s_waitcnt(0);
+    if (__any(ra.sc | rb.sc)) {
+      if (s2_rescale(ra)) load(q0, true, true, ia);
+      if (s2_rescale(rb)) load(q0 + LANES, true, true, ib);
     }
   }
 }
@@ -303,9 +335,7 @@ __global__ void __launch_bounds__(S2_WAVES * LANES) spin2_synthesis_kernel(PlanD
       {
         const double A = sA[t0 + j], B = sB[t0 + j];
         const double2 e = se[t0 + j], b = sb[t0 + j];
-        const double tp = fma(A, r.z, B), tm = fma(A, r.z, -B);
-        r.ep = fma(tp, r.op, -r.ep);
-        r.em = fma(tm, r.om, -r.em);
+        s2_even(r, A, B);
         const double sg = r.ep + r.em, dl = r.ep - r.em;
         EQr = fma(e.x, sg, EQr);
         EQi = fma(e.y, sg, EQi);
@@ -319,9 +349,7 @@ __global__ void __launch_bounds__(S2_WAVES * LANES) spin2_synthesis_kernel(PlanD
       {
         const double A = sA[t0 + j + 1], B = sB[t0 + j + 1];
         const double2 e = se[t0 + j + 1], b = sb[t0 + j + 1];
-        const double tp = fma(A, r.z, B), tm = fma(A, r.z, -B);
-        r.op = fma(tp, r.ep, -r.op);
-        r.om = fma(tm, r.em, -r.om);
+        s2_odd(r, A, B);
         const double sg = r.op + r.om, dl = r.op - r.om;
         OQr = fma(e.x, sg, OQr);
         OQi = fma(e.y, sg, OQi);
@@ -461,7 +489,7 @@ __global__ void __launch_bounds__(PC_WG) pol_coeff_kernel(PlanDev P, Leg64Dev L,
 hipError_t launch_spin2_analysis(const PlanDev& P, const Spin2Dev& S2, int nmaps, const double* G, double* partial_eb,
                                  int nblk2, hipStream_t s) {
   if (S2.nitems == 0) return hipSuccess;
-  hipLaunchKernelGGL(spin2_analysis_kernel, dim3(S2.nitems, nmaps), dim3(S2_WAVES * LANES), 0, s, P, S2, G, partial_eb,
+  hipLaunchKernelGGL(spin2_analysis_kernel, dim3(S2.nitems, nmaps), dim3(S2_AWAVES * LANES), 0, s, P, S2, G, partial_eb,
                      nblk2);
   return hipGetLastError();
 }
