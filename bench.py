@@ -26,7 +26,7 @@ PEAK_FP64_TFLOPS = 78.6     # 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz (vec
 PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_TFLOPS = {"f32": 157.3, "bf16x3": 2500.0, "bf16x6": 2500.0}   # dense matrix-core peaks
 MFMA_PRODUCTS = {"f32": 1, "bf16x3": 3, "bf16x6": 6}
-REC_FLOPS = 2               # FP64: u = (a z^2 + b) u1 - u2, two FMAs for two values of l
+REC_FLOPS = 3               # mu = (A z) mu1 - mu2: one multiply + one FMA per value
 CON_FLOPS = 4               # one complex-by-real multiply-accumulate per (l, m, ring pair)
 
 
@@ -431,7 +431,7 @@ def run_pol(args, np, torch, mwf, synth, dev):
     ana = st.ms_analysis / max(st.n_analysis, 1)
     syn = st.ms_synthesis / max(st.n_synthesis, 1)
     ring = st.ms_ring / max(st.n_ring, 1)
-    # per (l, m, ring pair): spin-0 T 6 flops; spin-2 E/B analysis 24 (two recurrences of
+    # per (l, m, ring pair): spin-0 T 7 flops; spin-2 E/B analysis 24 (two recurrences of
     # two multiply-adds, eight multiply-adds into E and B), synthesis 26 (plus sum and difference)
     ana_flops = (REC_FLOPS + CON_FLOPS + 24) * units
     syn_flops = (REC_FLOPS + CON_FLOPS + 26) * units

@@ -110,7 +110,7 @@ size_t plan_buffer_bytes(int nside, int lmax, int dtype, int nmaps) {
   return b;
 }
 
-// Device bytes of the shared tables of one (nside, lmax) geometry (fp64: with the FP64 Legendre tables).
+// Device bytes of the shared tables of one (nside, lmax) geometry (fp64: with the FP64 Legendre work lists).
 size_t geometry_bytes(int nside, int lmax, bool fp64) {
   const size_t nalm = (size_t)(lmax + 1) * (lmax + 2) / 2;
   const size_t rows = nalm + (size_t)(lmax + 1) * ROW_PAD;
@@ -121,11 +121,11 @@ size_t geometry_bytes(int nside, int lmax, bool fp64) {
       while (M < (size_t)(8 * i - 1)) M <<= 1;
       blue += M + 4 * i;
     }
-  // FP64 Legendre tables: factors per row, and a start state per ring pair of every work item (at
+  // FP64 Legendre work lists: a start state per ring pair of every work item (at
   // most one analysis item per (m, block) and 32 l, two per wave of a full launch beyond that)
   const size_t items = std::min<size_t>(5 * nalm / 16, (size_t)(lmax + 1) * ((nside + 127) / 128) + 8192) +
                        (size_t)(lmax + 1) * ((nside + 127) / 128);
-  const size_t leg64 = fp64 ? rows * 40 + items * std::min(2 * nside + 63, 256) * 17 : 0;
+  const size_t leg64 = fp64 ? items * std::min(2 * nside + 63, 256) * 17 : 0;
   return 2 * rows * 8 + blue * 24 + (size_t)(lmax + 1) * 64 + (size_t)(16 * nside + 64) * 24 +
          5 * nalm + leg64 + 256 * 1024;
 }

@@ -466,42 +466,9 @@ std::vector<Item64> pack_items(const std::vector<Item64>& items, const std::vect
   return packed;
 }
 
-// Tables and work lists of the FP64 Legendre kernels (Leg64Dev), made for the first FP64
-// plan of the shape; recurrence and factors as derived in phase_a.hip.
+// Work lists of the FP64 Legendre kernels (Leg64Dev), made for the first FP64 plan of the shape.
 int build_leg64(Geometry& g) {
   const int lmax = g.lmax, nbm = g.nblk_max_ana;
-  std::vector<double> ab[3];             // by form: MID, EQ, CAP
-  for (auto& t : ab) t.assign(g.rows_total, 0.0);
-  std::vector<double2> co(g.rows_total, make_double2(0.0, 0.0));
-  {
-    std::vector<long double> eps(lmax + 2), c((size_t)lmax / 2 + 2);
-    int64_t off = 0;
-    for (int m = 0; m <= lmax; ++m) {
-      const int nl = lmax - m + 1;
-      // eps_l at index l - m, l = m .. lmax + 1
-      for (int i = 0; i <= nl; ++i)
-        eps[i] = sqrtl((long double)i * (2.0L * m + i) / (4.0L * (m + i) * (m + i) - 1.0L));
-      eps[0] = 0.0L;
-      c[0] = 1.0L / eps[1];
-      co[off] = make_double2(1.0, 0.0);       // eps_{m+1} c_0
-      if (nl > 1) co[off + 1] = make_double2((double)c[0], 0.0);
-      for (int k = 1; 2 * k < nl; ++k) {
-        const int i = 2 * k;                   // l - m of the even function; u_k = (a z^2 + b) u_{k-1} - u_{k-2}
-        const long double w = eps[i] * eps[i + 1];
-        c[k] = k == 1 ? c[0] : c[k - 2] * eps[i - 1] * eps[i - 2] / w;
-        const long double a = c[k - 1] / (c[k] * w);
-        const long double b = -a * (eps[i] * eps[i] + eps[i - 1] * eps[i - 1]);
-        ab[0][off + i] = (double)a;
-        ab[0][off + i + 1] = (double)b;
-        ab[1][off + i] = ab[2][off + i] = (double)-a;
-        ab[1][off + i + 1] = (double)-(b + 2.0L);
-        ab[2][off + i + 1] = (double)(a + b - 2.0L);
-        co[off + i] = make_double2((double)(eps[i + 1] * c[k]), (double)(eps[i] * c[k - 1]));
-        if (i + 1 < nl) co[off + i + 1] = make_double2((double)c[k], 0.0);
-      }
-      off += nl + ROW_PAD;
-    }
-  }
   // (m, block of rb pairs) with the first l - m, in chunks of 16, at which a ring pair of it exceeds
   // 2^-128, and the l - m up to which a ring of it is still scaled
   std::vector<uint16_t> wake, rise;
@@ -579,16 +546,11 @@ int build_leg64(Geometry& g) {
   for (int q = 0; q < g.npairs; ++q) z[q] = ring_geometry(g.nside, 2 * g.nside - q).z;
 
   DevMem& M = g.mem;
-  double *dab[3] = {}, *dz = nullptr;
-  double2* dco = nullptr;
+  double* dz = nullptr;
   int32_t* dstart = nullptr;
   int rc;
-  if ((rc = M.upload(&dab[0], ab[0])) || (rc = M.upload(&dab[1], ab[1])) || (rc = M.upload(&dab[2], ab[2])) ||
-      (rc = M.upload(&dco, co)) || (rc = M.upload(&dz, z)) || (rc = M.upload(&dstart, start)))
-    return rc;
+  if ((rc = M.upload(&dz, z)) || (rc = M.upload(&dstart, start))) return rc;
   Leg64Dev L{};
-  for (int f = 0; f < 3; ++f) L.ab[f] = dab[f];
-  L.co = dco;
   L.z = dz;
   L.start = dstart;
   PlanDev D{};
@@ -596,6 +558,7 @@ int build_leg64(Geometry& g) {
   D.lmax = lmax;
   D.npairs = g.npairs;
   D.pairs = g.pairs;
+  D.A = g.A;
   D.row_off = g.row_off;
   D.norm_m = g.norm;
   D.n_active = g.nact;
@@ -614,7 +577,7 @@ int build_leg64(Geometry& g) {
     T.nwg = (int)wg.size() - 1;
     T.waves = waves;
     T.rb = rb;
-    MWF_HIP(launch_start_state(D, L, T, (int)it.size(), CHUNK, ds, dc, nullptr));
+    MWF_HIP(launch_start_state(D, T, (int)it.size(), CHUNK, ds, dc, nullptr));
     T.state = ds;
     T.scale = dc;
     return WF_OK;

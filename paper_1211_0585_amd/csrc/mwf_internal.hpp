@@ -156,7 +156,7 @@ struct Item64 {
 
 // Work list of one FP64 Legendre launch: workgroup b, `waves` waves, shares items[wg[b] ..
 // wg[b + 1]); state and scale hold rb entries per item, the recurrence state
-// (u of odd and even k; the two registers of the equatorial form) of its pairs at i0.
+// (the mu of the two l before i0 and their common scale) of its pairs.
 struct Leg64List {
   const Item64* items;
   const int32_t* wg;
@@ -165,12 +165,8 @@ struct Leg64List {
   int32_t nwg, waves, rb, pad_;
 };
 
-// FP64 Legendre tables of one geometry (see phase_a.hip): recurrence and conversion factors in
-// the padded row layout, and the work lists. Made for the first FP64 plan of a shape.
+// FP64 Legendre work lists of one geometry (see phase_a.hip), made for the first FP64 plan of a shape.
 struct Leg64Dev {
-  const double* ab[3];     // [rows_total] per form (MID, EQ, CAP): in the slots l - m = 2k and 2k + 1 of the row
-                           // of m, a_k and b_k; -a_k and -(b_k + 2); -a_k and a_k + b_k - 2
-  const double2* co;       // [rows_total] (alpha_i, beta_i): a_lm = alpha_i P_i + beta_i P_{i-2}, i = l - m
   const double* z;         // [npairs] z of the north ring
   const int32_t* start;    // [lmax+1][nblk_max] first l - m summed by the analysis in each block
   Leg64List ana, syn;
@@ -368,9 +364,9 @@ hipError_t launch_legendre_analysis_f64(const PlanDev& P, const Leg64Dev& L, int
                                         double2* partial, hipStream_t s);
 
 enum SynthMode : int32_t {
-  SY_FROM_PARTIAL = 0,   // a from the partial sums; s = f(lambda) a; synthesise s
+  SY_FROM_PARTIAL = 0,   // a = C sum(partials); s = f(lambda) a; synthesise s
   SY_FROM_ALM = 1,       // synthesise the caller's alm
-  SY_ALM_ONLY = 2        // a from the partial sums -> alm output, no synthesis
+  SY_ALM_ONLY = 2        // a = C sum(partials) -> alm output, no synthesis
 };
 
 struct SynthArgs {
@@ -380,7 +376,7 @@ struct SynthArgs {
   const double2* partial;   // [map][blk][nalm]
   const double2* alm_in;    // [map][nalm]
   double2* alm_out;         // [map][nalm] or null
-  double2* bcoef;           // [map][rows_total] synthesis coefficients in the padded row layout
+  double2* bcoef;           // [map][rows_total] C_l s_lm in the padded row layout
   double* F;                // [map][pair][m][4]
   double* chi2;             // null, or where map 0 adds sum_lm w_m |s_lm|^2 / C_l (SY_FROM_PARTIAL)
   int64_t chi2_stride;
@@ -567,7 +563,7 @@ struct PolCoeffArgs {
   const int32_t* nblk2_m;     // [lmax+1] E/B blocks written for m
   const double2* alm_in;      // [map][3][nalm]
   double2* alm_out;           // [map][3][nalm] or null
-  double2* bcoef_t;           // [map][rows_total]: spin-0 synthesis coefficients of s_T
+  double2* bcoef_t;           // [map][rows_total]: C_l s_T (spin-0 synthesis input)
   double2* bcoef_eb;          // [map][rows_total][2]: -K s_E / 2, -K s_B / 2
   const double* cl4;          // [4][lmax+1] TT, EE, BB, TE
 };
@@ -581,9 +577,9 @@ hipError_t launch_spin2_synthesis(const PlanDev& P, const Spin2Dev& S2, int nmap
 // Plan-time, per (m, ring pair): where lambda_lm leaves the scaled range and where it exceeds
 // 2^-128, or WAKE_NEVER (polar skip, start and cost of the FP64 work items).
 hipError_t launch_reach(const PlanDev& P, uint16_t* wake, uint16_t* rise, hipStream_t s);
-// Plan-time: state and scale of a work list, from its items and the tables of L.
-hipError_t launch_start_state(const PlanDev& P, const Leg64Dev& L, const Leg64List& T, int nitems, int ch,
-                              double2* state, uint8_t* scale, hipStream_t s);
+// Plan-time: state and scale of a work list, from its items.
+hipError_t launch_start_state(const PlanDev& P, const Leg64List& T, int nitems, int ch, double2* state, uint8_t* scale,
+                              hipStream_t s);
 // Raise the dynamic-LDS limit of `kernel` on the current device to at least `lds` (never lower it).
 hipError_t ensure_dynamic_lds(const void* kernel, size_t lds);
 

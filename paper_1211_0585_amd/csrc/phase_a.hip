@@ -11,29 +11,20 @@
 //
 // using lambda_lm(-z) = (-1)^(l+m) lambda_lm(z) for the mirror rings.
 //
-// Two values of l per recurrence step (Ishioka 2018, J. Meteorol. Soc. Japan 96, 241). With
-// eps_l = sqrt((l^2 - m^2) / (4 l^2 - 1)), z lambda_l = eps_{l+1} lambda_{l+1} + eps_l lambda_{l-1},
-// and the even polynomials p_k = lambda_{m+2k+1} / z one has
-//   lambda_{m+2k+1} = z p_k,   lambda_{m+2k} = eps_{m+2k+1} p_k + eps_{m+2k} p_{k-1},
-//   eps_{l+1} eps_{l+2} p_{k+1} = (z^2 - eps_{l+1}^2 - eps_l^2) p_k - eps_l eps_{l-1} p_{k-1}
-// (l = m + 2k + 1). Rescaled, p_k = c_k u_k, this is u_k = (a_k z^2 + b_k) u_{k-1} - u_{k-2}:
-// two FMAs for the pair (l, l + 1), where the step in l took a multiply and an FMA for each.
-// The ring sums then run on u_k alone, S_k = sum u_k S and T_k = sum u_k (z D), and the
-// coefficient kernel turns them into alm (and alm into the synthesis coefficients) with two
-// factors per l:  a_{m+2k} = eps_{m+2k+1} c_k S_k + eps_{m+2k} c_{k-1} S_{k-1}, a_{m+2k+1} = c_k T_k.
-// FP64 operations per (l, m, ring pair): 1 in the recurrence and 2 in the sums, against 2 and 2.
-// FP64 issue bounds both kernels (the FP64 matrix instructions share the same units: a probe
-// with both in flight took the sum of their times), so the operations left out are the gain.
+// The recurrence runs on rescaled values mu_l = lambda_lm / C_lm that obey
+//   mu_l = (A_lm z) mu_{l-1} - mu_{l-2}
+// (A and C are plan-time FP64 tables derived from
+//  a_lm = sqrt((4 l^2 - 1)/(l^2 - m^2)) with C_l = C_{l-2} a_l / a_{l-1}, A_l = a_l C_{l-1} / C_l),
+// i.e. one multiply and one FMA per value; C is applied once per (l, m) after the
+// ring sum (analysis) or folded into s_lm (synthesis).
 //
-// Near the equator a z^2 + b comes close to -2 and towards the poles to +2, where rounding
-// grows along the recurrence like 1 / sin(2 theta). The first 256 ring pairs therefore carry
-// v_k = u_k + u_{k-1}, with alternating signs folded in (ut_k = (-1)^k u_k, vt likewise), and
-// the blocks of the polar caps the differences v_k = u_k - u_{k-1}:
-//   equator  vt_{k+1} = vt_k - (a_k z^2 + b_k + 2) ut_k,              ut_{k+1} = ut_k + vt_{k+1}
-//   caps     v_{k+1} = v_k + (a_k + b_k - 2 - a_k sin^2 theta) u_k,    u_{k+1} = u_k + v_{k+1}
-// (two FMAs and an add for the step). Error of the transform pair at Nside 1024 against 64-bit
-// sums: 2.1e-14; 5.3e-14 with the plain form everywhere, 1.5e-14 with the step in l. (Nside 512, eight
-// sweeps: 0.9e-14 against 1.1e-14.)
+// Two values of l per step (Ishioka 2018, J. Meteorol. Soc. Japan 96, 241: a recurrence in z^2 for
+// lambda_{m+2k+1} / z, from which the even functions follow as a combination of two) take half of
+// these operations, and were measured and taken back: the even functions are then differences of
+// values l times larger next to the equator, and elsewhere the step's coefficients cost digits.
+// Relative error of the lambda_lm of one ring over all l and m, in FP64 against 80 bits, Nside 512,
+// lmax 1024, pairs 0, 16, 64, 256, 512, 800 from the equator on: 5e-17, 5e-16, 6e-16, 1.6e-15, 3.7e-15,
+// 9e-15 with the step in l; 1e-13, 9e-15, 2.4e-15, 5e-15, 1.5e-14, 5e-14 with the best form of the other.
 //
 // The sectoral seed lambda_mm = norm_m sin^m(theta) underflows FP64 near the
 // poles: every value carries an integer scale s (value = v 2^(-512 s)). The scale
@@ -41,7 +32,7 @@
 // a ring whose scale is still positive at the start of a chunk contributes
 // nothing in that chunk (its values are below 2^-448 times the growth of one
 // chunk, far under FP64 resolution of the sums). The recurrence alternates
-// between two registers, so a step has no moves.
+// between two registers, so a step is one multiply and one FMA and no moves.
 //
 // Work items are (m, block of 64 R ring pairs, range of l), one wavefront each; a lane owns R
 // ring pairs. An item starts from a recurrence state made at plan time, so its seeds cost a
@@ -89,55 +80,35 @@ __device__ __forceinline__ double fold_halves(double a, double b) {
   return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
 }
 
-// Forms of the recurrence (see above) and the form of a block of rb ring pairs.
-enum Form { MID = 0, EQ = 1, CAP = 2 };
-__device__ __forceinline__ int block_form(const PlanDev& P, int blk, int rb) {
-  return (blk + 1) * rb <= 256 ? EQ : (blk * rb >= P.nside ? CAP : MID);
-}
-
-// Recurrence state of a lane's ring pairs: z^2 (sin^2 theta in the CAP form), the two registers
-// (u of the latest odd and even k, or u and v), and the scales.
+// Recurrence state of a lane's ring pairs: z, the two registers (mu of the latest odd and even
+// l - m), and the scales.
 template <int R>
 struct RingState {
-  double zz[R], u1[R], u2[R];
+  double z[R], mu1[R], mu2[R];
   unsigned sc;   // a byte per ring pair (at most four)
 };
 
 // The plan's start state of item k (zero past the active ring pairs).
-template <int R, int FORM>
+template <int R>
 __device__ __forceinline__ void init_rings(const PlanDev& P, const Leg64List& T, const double* __restrict__ zt, int k,
-                                           int blk, int lane, int nact, RingState<R>& st, double (&z)[R]) {
+                                           int blk, int lane, int nact, RingState<R>& st) {
   st.sc = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int q = blk * (LANES * R) + r * LANES + lane;
     const size_t at = (size_t)k * (LANES * R) + r * LANES + lane;
-    const double2 u = T.state[at];
-    z[r] = q < nact ? zt[min(q, P.npairs - 1)] : 0.0;
-    st.zz[r] = FORM == CAP ? (1.0 - z[r]) * (1.0 + z[r]) : z[r] * z[r];
-    st.u1[r] = u.x;
-    st.u2[r] = u.y;
+    const double2 mu = T.state[at];
+    st.z[r] = q < nact ? zt[min(q, P.npairs - 1)] : 0.0;
+    st.mu1[r] = mu.x;
+    st.mu2[r] = mu.y;
     st.sc |= (unsigned)T.scale[at] << (8 * r);
   }
 }
 
-// One step pair (k even, then odd) of a ring: use(0, u_k) and use(1, u_{k+1}, or -u_{k+1} in the
-// EQ form); c0 and c1 the coefficients of the two steps in the table of the form.
-template <int FORM, class Use>
-__device__ __forceinline__ void step_pair(double& u1, double& u2, double zz, double2 c0, double2 c1, Use use) {
-  if constexpr (FORM != MID) {
-    u2 = fma(fma(c0.x, zz, c0.y), u1, u2);   // u2 = v, u1 = u
-    u1 = u1 + u2;
-    use(0, u1);
-    u2 = fma(fma(c1.x, zz, c1.y), u1, u2);
-    u1 = u1 + u2;
-    use(1, u1);                              // (EQ: -u_k)
-  } else {
-    u2 = fma(fma(c0.x, zz, c0.y), u1, -u2);
-    use(0, u2);
-    u1 = fma(fma(c1.x, zz, c1.y), u2, -u1);
-    use(1, u1);
-  }
+// Steps to l (l - m even, into mu2) and l + 1 (into mu1) of a ring.
+__device__ __forceinline__ void step_pair(double& mu1, double& mu2, double z, double A0, double A1) {
+  mu2 = fma(A0 * z, mu1, -mu2);
+  mu1 = fma(A1 * z, mu2, -mu1);
 }
 
 // Once per chunk: bring large scaled values back by 2^-512. Returns a bit mask of
@@ -147,9 +118,9 @@ __device__ __forceinline__ int rescale_chunk(RingState<R>& st) {
   int woke = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    if (((st.sc >> (8 * r)) & 0xff) != 0 && fmax(fabs(st.u1[r]), fabs(st.u2[r])) > BIG_THRESH) {
-      st.u1[r] *= RESCALE;
-      st.u2[r] *= RESCALE;
+    if (((st.sc >> (8 * r)) & 0xff) != 0 && fmax(fabs(st.mu1[r]), fabs(st.mu2[r])) > BIG_THRESH) {
+      st.mu1[r] *= RESCALE;
+      st.mu2[r] *= RESCALE;
       st.sc -= 1u << (8 * r);
       if (((st.sc >> (8 * r)) & 0xff) == 0) woke |= 1 << r;
     }
@@ -189,7 +160,7 @@ struct ItemQueue {
   }
 };
 
-template <int R, int FORM>
+template <int R>
 __device__ __forceinline__ void analysis_item(const PlanDev& P, const Leg64Dev& L, const int k, const Item64 it,
                                               const int map, const int lane, double* __restrict__ lds,
                                               const double* __restrict__ G, double2* __restrict__ partial) {
@@ -197,14 +168,13 @@ __device__ __forceinline__ void analysis_item(const PlanDev& P, const Leg64Dev& 
   double* sA = lds + 2 * ACH * RED_STRIDE;
   const int m = it.m, blk = it.blk;
   const int nact = P.n_active[m];
-  const double* __restrict__ Arow = L.ab[FORM] + P.row_off[m] + it.i0;
+  const double* __restrict__ Arow = P.A + P.row_off[m] + it.i0;
   const size_t pstride = gf_stride(P.lmax);
   const double* Gm = G + (size_t)map * P.npairs * pstride + (size_t)m * 4;
 
   RingState<R> st;
-  double z[R];
-  init_rings<R, FORM>(P, L.ana, L.z, k, blk, lane, nact, st, z);
-  // S and z D of each ring, zero while the ring's values are still scaled
+  init_rings<R>(P, L.ana, L.z, k, blk, lane, nact, st);
+  // S and D of each ring, zero while the ring's values are still scaled
   double Sre[R], Sim[R], Dre[R], Dim[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -214,8 +184,8 @@ __device__ __forceinline__ void analysis_item(const PlanDev& P, const Leg64Dev& 
     const bool on = q < nact && ((st.sc >> (8 * r)) & 0xff) == 0;
     Sre[r] = on ? sd.x : 0.0;
     Sim[r] = on ? sd.y : 0.0;
-    Dre[r] = on ? z[r] * sd.z : 0.0;
-    Dim[r] = on ? z[r] * sd.w : 0.0;
+    Dre[r] = on ? sd.z : 0.0;
+    Dim[r] = on ? sd.w : 0.0;
   }
 
   // the item's part of the block's partial sums
@@ -223,12 +193,11 @@ __device__ __forceinline__ void analysis_item(const PlanDev& P, const Leg64Dev& 
   double* out = reinterpret_cast<double*>(partial + ((size_t)map * P.nblk_max + blk) * P.nalm +
                                           alm_index(P.lmax, m, m) + it.i0);
 
-  // recurrence coefficients of LTILE values of l (the two factors of step k in the slots of
-  // l - m = 2k and 2k + 1): lane i loads slot base + i one tile ahead, the tile in use is read
-  // from LDS (the same address in every lane). The loads are unconditional, with the index
-  // clamped to the row's end (past it all slots are zero), so that no wait for them lands
-  // inside the loop.
-  const int na = P.lmax - m + 2 - it.i0;
+  // recurrence coefficients of LTILE values of l: lane i loads l = base + i one tile ahead, the
+  // tile in use is read from LDS (the same address in every lane). The loads are unconditional,
+  // with the index clamped to the first entry of the row's zero padding, so that no wait for
+  // them lands inside the loop.
+  const int na = P.lmax - m + 1 - it.i0;
   auto tile_a = [&](int i) { return Arow[min(i, na)]; };
   sA[lane] = tile_a(lane);
   // every load issued so far (ring states, S/D, tile 0) completes here, so the loop
@@ -250,17 +219,20 @@ __device__ __forceinline__ void analysis_item(const PlanDev& P, const Leg64Dev& 
     const double2* Ac = reinterpret_cast<const double2*>(sA + t0);
 #pragma unroll
     for (int j = 0; j < ACH; j += 4) {
-      const double2 c0 = Ac[j / 2], c1 = Ac[j / 2 + 1];
+      const double2 A0 = Ac[j / 2], A1 = Ac[j / 2 + 1];
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        step_pair<FORM>(st.u1[r], st.u2[r], st.zz[r], c0, c1, [&](int h, double x) {
-          const int v = j + 2 * h;
-          const double u = FORM == EQ && h == 1 ? -x : x;
-          are[v] = fma(u, Sre[r], are[v]);
-          aim[v] = fma(u, Sim[r], aim[v]);
-          are[v + 1] = fma(u, Dre[r], are[v + 1]);
-          aim[v + 1] = fma(u, Dim[r], aim[v + 1]);
-        });
+      for (int h = 0; h < 2; ++h) {
+        const int v = j + 2 * h;
+        const double2 A = h ? A1 : A0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          step_pair(st.mu1[r], st.mu2[r], st.z[r], A.x, A.y);
+          are[v] = fma(st.mu2[r], Sre[r], are[v]);
+          aim[v] = fma(st.mu2[r], Sim[r], aim[v]);
+          are[v + 1] = fma(st.mu1[r], Dre[r], are[v + 1]);
+          aim[v + 1] = fma(st.mu1[r], Dim[r], aim[v + 1]);
+        }
+      }
       // keeps the tile reads of all the steps from moving up here, where they cost the
       // registers that let a third wave in
       if (j == ACH / 2) __builtin_amdgcn_sched_barrier(0);
@@ -295,11 +267,10 @@ __device__ __forceinline__ void analysis_item(const PlanDev& P, const Leg64Dev& 
         if (woke & (1 << r)) {
           const int q = blk * (LANES * R) + r * LANES + lane;
           const double4 sd = *reinterpret_cast<const double4*>(Gm + (size_t)q * pstride);
-          const double zq = L.z[q];
           Sre[r] = sd.x;
           Sim[r] = sd.y;
-          Dre[r] = zq * sd.z;
-          Dim[r] = zq * sd.w;
+          Dre[r] = sd.z;
+          Dim[r] = sd.w;
         }
       // (rare) complete these loads here rather than at their first use, where the
       // wait would also cover the tile prefetch
@@ -320,91 +291,53 @@ __global__ void __launch_bounds__(FP64_ANA_WAVES * LANES) legendre_analysis_f64_
   double* lds = leg64_lds + 2 + wave * ANA_LDS;
   for (ItemQueue q(L.ana, leg64_lds); q.next(lane);) {
     const int k = q.k;
-    const Item64 it = L.ana.items[k];
-    switch (block_form(P, it.blk, LANES * R)) {
-      case EQ: analysis_item<R, EQ>(P, L, k, it, blockIdx.y, lane, lds, G, partial); break;
-      case CAP: analysis_item<R, CAP>(P, L, k, it, blockIdx.y, lane, lds, G, partial); break;
-      default: analysis_item<R, MID>(P, L, k, it, blockIdx.y, lane, lds, G, partial);
-    }
+    analysis_item<R>(P, L, k, L.ana.items[k], blockIdx.y, lane, lds, G, partial);
   }
 }
 
-// Filtered coefficients for the synthesis, one thread per (l, m, map), from the sums
-// P_i of the blocks (i = l - m; S_k at i = 2k, T_k at i = 2k + 1) and the plan's factors:
-//   SY_FROM_PARTIAL  a_i = alpha_i P_i + beta_i P_{i-2}, s = f_l(lambda) a
-//   SY_ALM_ONLY      the same a (the forward transform), s = a
+// Filtered coefficients for the synthesis, one thread per (l, m, map):
+//   SY_FROM_PARTIAL  a = C_l sum_blk partial, s = f_l(lambda) a
+//   SY_ALM_ONLY      a = C_l sum_blk partial (the forward transform), s = a
 //   SY_FROM_ALM      s = caller's alm (imaginary part of m = 0 dropped)
-// s goes to alm_out when requested; bcoef_i = alpha_i s_i + beta_{i+2} s_{i+2} (the transpose;
-// beta is zero at odd i and in the padding), in the padded row layout of the recurrence
-// tables (zeros beyond lmax) so the synthesis can read whole chunks.
+// s goes to alm_out when requested; bcoef = C_l s, in the padded row layout of
+// the recurrence tables (zeros beyond lmax) so the synthesis can read whole chunks.
 // A flat grid over the padded rows r of every m (m = row_m[r], l = m + r - row_off[m];
 // padding rows get zeros) and the maps: with one workgroup per m instead, the long rows
-// of small m went to a few waves in turn, each waiting on its loads. A workgroup writes
-// COEFF_ROWS rows and forms P and s for two more on either side, the neighbours its own need
-// (exchanged through LDS; 1.6 % more reads than rows).
-constexpr int COEFF_WG = 256, COEFF_ROWS = COEFF_WG - 4;
-
-__global__ void __launch_bounds__(COEFF_WG) legendre_coeff_kernel(PlanDev P, Leg64Dev L, SynthArgs a) {
-  __shared__ double2 sP[COEFF_WG], sS[COEFF_WG];
-  const int t = threadIdx.x;
-  const int64_t r = (int64_t)blockIdx.x * COEFF_ROWS + t - 2;
+// of small m went to a few waves in turn, each waiting on its loads.
+__global__ void legendre_coeff_kernel(PlanDev P, Leg64Dev L, SynthArgs a) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int map = blockIdx.y;
-  const bool own = t >= 2 && t < 2 + COEFF_ROWS && r < P.rows_total;
   const bool chi = a.chi2 != nullptr && a.mode == SY_FROM_PARTIAL;
   double chi_acc = 0.0;
-  const int lmax = P.lmax;
-  int m = 0, i = 0;
-  bool val = false;
-  double2 co = make_double2(0.0, 0.0);
-  if (r >= 0 && r < P.rows_total) {
-    m = P.row_m[r];
-    i = (int)(r - P.row_off[m]);
-    val = i < lmax - m + 1;
-    if (val) co = L.co[r];
-  }
-  const int64_t at = alm_index(lmax, m, m) + i;
-  double2 p = make_double2(0.0, 0.0), s = p;
-  if (a.mode == SY_FROM_ALM) {
-    if (val) {
-      s = a.alm_in[(size_t)map * P.nalm + at];
-      if (m == 0) s.y = 0.0;
-    }
-  } else {
-    if (val) p = block_partials(P, L, a.partial + (size_t)map * P.nblk_max * P.nalm + at, m, i);
-    sP[t] = p;
-    __syncthreads();
-    if (val && t >= 2) {
-      // the ring phase already applied Omega to G
-      s = make_double2(co.x * p.x, co.x * p.y);
-      if (co.y != 0.0) {
-        const double2 q = sP[t - 2];
-        s.x = fma(co.y, q.x, s.x);
-        s.y = fma(co.y, q.y, s.y);
+  if (r < P.rows_total) {
+    const int lmax = P.lmax;
+    const int m = P.row_m[r];
+    const int i = (int)(r - P.row_off[m]);
+    double2 b = make_double2(0.0, 0.0);
+    if (i < lmax - m + 1) {
+      const int64_t at = alm_index(lmax, m, m) + i;
+      const double c = P.C[r];
+      double2 alm;
+      if (a.mode == SY_FROM_ALM) {
+        alm = a.alm_in[(size_t)map * P.nalm + at];
+        if (m == 0) alm.y = 0.0;
+      } else {
+        // the ring phase already applied Omega to G
+        const double2 p = block_partials(P, L, a.partial + (size_t)map * P.nblk_max * P.nalm + at, m, i);
+        alm = make_double2(p.x * c, p.y * c);
+        if (a.mode == SY_FROM_PARTIAL) {
+          const double cl = P.cl[m + i];
+          const double f = cl > 0.0 ? cl / (cl + a.lambda * P.tau * P.omega) : 0.0;
+          alm.x *= f;
+          alm.y *= f;
+          // chi^2 prior term of the new iterate: w_m |s_lm|^2 / C_l (w = 1 at m = 0, else 2)
+          if (chi && cl > 0.0) chi_acc = (m == 0 ? 1.0 : 2.0) * (alm.x * alm.x + alm.y * alm.y) / cl;
+        }
       }
-      if (a.mode == SY_FROM_PARTIAL) {
-        const double cl = P.cl[m + i];
-        const double f = cl > 0.0 ? cl / (cl + a.lambda * P.tau * P.omega) : 0.0;
-        s.x *= f;
-        s.y *= f;
-        // chi^2 prior term of the new iterate: w_m |s_lm|^2 / C_l (w = 1 at m = 0, else 2)
-        if (chi && own && cl > 0.0) chi_acc = (m == 0 ? 1.0 : 2.0) * (s.x * s.x + s.y * s.y) / cl;
-      }
+      if (a.alm_out) a.alm_out[(size_t)map * P.nalm + at] = alm;
+      b = make_double2(alm.x * c, alm.y * c);
     }
-  }
-  if (own && val && a.alm_out) a.alm_out[(size_t)map * P.nalm + at] = s;
-  if (a.mode != SY_ALM_ONLY) {
-    sS[t] = s;
-    __syncthreads();
-    if (own) {
-      double2 b = make_double2(co.x * s.x, co.x * s.y);
-      const double beta = val ? L.co[r + 2].y : 0.0;   // (a row ends in padding: r + 2 stays inside it)
-      if (beta != 0.0) {
-        const double2 n = sS[t + 2];
-        b.x = fma(beta, n.x, b.x);
-        b.y = fma(beta, n.y, b.y);
-      }
-      a.bcoef[(size_t)map * P.rows_total + r] = b;
-    }
+    if (a.mode != SY_ALM_ONLY) a.bcoef[(size_t)map * P.rows_total + r] = b;
   }
   if (chi) block_sum_add(chi_acc, a.chi2 + map * a.chi2_stride);
 }
@@ -412,65 +345,57 @@ __global__ void __launch_bounds__(COEFF_WG) legendre_coeff_kernel(PlanDev P, Leg
 constexpr int SCH = 16;   // synthesis: values of l per coefficient tile and scale check
 static_assert(LTILE % SCH == 0 && SCH == CHUNK, "synthesis chunking");
 
-// e_r += +-u_r b_V and o_r += +-u_r b_{V+1} (complex b) for the R ring pairs of a lane. Lane i of
+// e_r += u_r b_V and o_r += w_r b_{V+1} (complex b) for the R ring pairs of a lane. Lane i of
 // every row of 16 holds b_i of a tile of 16; the FMAs take the lane of the row they need as an
 // operand (DPP row_newbcast), so the coefficients cost neither LDS nor registers: read from LDS
 // as broadcasts they took as long as the FP64 work (32 bytes per lane and FMA quartet, and one
 // LDS for four SIMDs), through the scalar cache every chunk waited on it. The s_nop covers a
 // write of bx or by just before (two wait states before a DPP read).
-#define MWF_FMAC(ACC, B, SGN, U, LANE) \
-  "\n\tv_fmac_f64_dpp %" ACC ", %" B ", " SGN "%" U " row_newbcast:%" LANE " row_mask:0xf bank_mask:0xf"
-#define MWF_RING(A0, A1, A2, A3, SGN, U) \
-  MWF_FMAC(A0, "[x]", SGN, U, "[v]")     \
-  MWF_FMAC(A1, "[y]", SGN, U, "[v]") MWF_FMAC(A2, "[x]", SGN, U, "[w]") MWF_FMAC(A3, "[y]", SGN, U, "[w]")
+#define MWF_FMAC(ACC, B, U, LANE) "\n\tv_fmac_f64_dpp %" ACC ", %" B ", %" U " row_newbcast:%" LANE " row_mask:0xf bank_mask:0xf"
+#define MWF_RING(A0, A1, A2, A3, U, W) \
+  MWF_FMAC(A0, "[x]", U, "[v]") MWF_FMAC(A1, "[y]", U, "[v]") MWF_FMAC(A2, "[x]", W, "[w]") MWF_FMAC(A3, "[y]", W, "[w]")
 #define MWF_OUT(r) "+v"(er[r]), "+v"(ei[r]), "+v"(orr[r]), "+v"(oi[r])
 #define MWF_IN [x] "v"(bx), [y] "v"(by), [v] "n"(V), [w] "n"(V + 1)
-#define MWF_ACCUMULATE(SGN)                                                                                       \
-  if constexpr (R == 1)                                                                                           \
-    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", SGN, "[p]") : MWF_OUT(0) : MWF_IN, [p] "v"(u[0]));         \
-  else if constexpr (R == 2)                                                                                      \
-    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", SGN, "[p]") MWF_RING("4", "5", "6", "7", SGN, "[q]")       \
-                 : MWF_OUT(0), MWF_OUT(1) : MWF_IN, [p] "v"(u[0]), [q] "v"(u[1]));                                 \
-  else                                                                                                            \
-    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", SGN, "[p]") MWF_RING("4", "5", "6", "7", SGN, "[q]")       \
-                 MWF_RING("8", "9", "10", "11", SGN, "[r]") MWF_RING("12", "13", "14", "15", SGN, "[s]")           \
-                 : MWF_OUT(0), MWF_OUT(1), MWF_OUT(2), MWF_OUT(3)                                                  \
-                 : MWF_IN, [p] "v"(u[0]), [q] "v"(u[1]), [r] "v"(u[2]), [s] "v"(u[3]));
-template <int V, bool NEG, int R>
+template <int V, int R>
 __device__ __forceinline__ void accumulate(double (&er)[R], double (&ei)[R], double (&orr)[R], double (&oi)[R],
-                                           const double (&u)[R], double bx, double by) {
+                                           const double (&u)[R], const double (&w)[R], double bx, double by) {
   static_assert(R == 1 || R == 2 || R == 4, "ring pairs per lane");
-  if constexpr (NEG) {
-    MWF_ACCUMULATE("-")
-  } else {
-    MWF_ACCUMULATE("")
-  }
+  if constexpr (R == 1)
+    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", "[u0]", "[w0]") : MWF_OUT(0) : MWF_IN, [u0] "v"(u[0]), [w0] "v"(w[0]));
+  else if constexpr (R == 2)
+    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", "[u0]", "[w0]") MWF_RING("4", "5", "6", "7", "[u1]", "[w1]")
+                 : MWF_OUT(0), MWF_OUT(1)
+                 : MWF_IN, [u0] "v"(u[0]), [w0] "v"(w[0]), [u1] "v"(u[1]), [w1] "v"(w[1]));
+  else
+    asm volatile("s_nop 1" MWF_RING("0", "1", "2", "3", "[u0]", "[w0]") MWF_RING("4", "5", "6", "7", "[u1]", "[w1]")
+                 MWF_RING("8", "9", "10", "11", "[u2]", "[w2]") MWF_RING("12", "13", "14", "15", "[u3]", "[w3]")
+                 : MWF_OUT(0), MWF_OUT(1), MWF_OUT(2), MWF_OUT(3)
+                 : MWF_IN, [u0] "v"(u[0]), [w0] "v"(w[0]), [u1] "v"(u[1]), [w1] "v"(w[1]), [u2] "v"(u[2]), [w2] "v"(w[2]),
+                   [u3] "v"(u[3]), [w3] "v"(w[3]));
 }
-#undef MWF_ACCUMULATE
 #undef MWF_IN
 #undef MWF_OUT
 #undef MWF_RING
 #undef MWF_FMAC
 
-template <int R, int FORM>
+template <int R>
 __device__ __forceinline__ void synthesis_item(const PlanDev& P, const Leg64Dev& L, const int k, const Item64 it,
                                                const int map, const int lane, double* __restrict__ sA,
                                                const double2* __restrict__ bcoef, double* __restrict__ F) {
   const int m = it.m, blk = it.blk;
   const int64_t roff = P.row_off[m] + it.i0;
-  const double* __restrict__ Arow = L.ab[FORM] + roff;
+  const double* __restrict__ Arow = P.A + roff;
   const double2* __restrict__ brow = bcoef + (size_t)map * P.rows_total + roff;
   const int nact = P.n_active[m];
   const int nl = it.i1 - it.i0;
   // recurrence coefficients of LTILE values of l: lane i loads l = base + i one tile ahead,
   // the tile in use is read from LDS (the same address in every lane); synthesis coefficients
   // of SCH values of l likewise, in registers. The loads are unconditional, with the index
-  // clamped into the row's zero padding.
-  auto tile_a = [&](int i) { return Arow[min(i, nl + 1)]; };
-  auto tile_b = [&](int i) { return brow[min(i + (lane & (SCH - 1)), nl + 1)]; };
+  // clamped to the first entry of the row's zero padding.
+  auto tile_a = [&](int i) { return Arow[min(i, nl)]; };
+  auto tile_b = [&](int i) { return brow[min(i + (lane & (SCH - 1)), nl)]; };
   RingState<R> st;
-  double z[R];
-  init_rings<R, FORM>(P, L.syn, L.z, k, blk, lane, nact, st, z);
+  init_rings<R>(P, L.syn, L.z, k, blk, lane, nact, st);
   sA[lane] = tile_a(lane);
   double2 b = tile_b(0);
   // every load issued so far (ring states, tile 0) completes here
@@ -493,14 +418,14 @@ __device__ __forceinline__ void synthesis_item(const PlanDev& P, const Leg64Dev&
     const unsigned scaled = st.sc;
     const double2* Ac = reinterpret_cast<const double2*>(sA + t0);
     auto step = [&](auto V) {
-      constexpr int v = decltype(V)::value;     // slots v, v + 1 (k even) and v + 2, v + 3 (k odd)
-      const double2 c0 = Ac[v / 2], c1 = Ac[v / 2 + 1];
-      double u[2][R];
+      constexpr int v = decltype(V)::value;     // l - m = i + v .. i + v + 3
+      const double2 A0 = Ac[v / 2], A1 = Ac[v / 2 + 1];
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        step_pair<FORM>(st.u1[r], st.u2[r], st.zz[r], c0, c1, [&](int h, double x) { u[h][r] = x; });
-      accumulate<v, false>(Ere, Eim, Ore, Oim, u[0], b.x, b.y);
-      accumulate<v + 2, FORM == EQ>(Ere, Eim, Ore, Oim, u[1], b.x, b.y);
+      for (int r = 0; r < R; ++r) step_pair(st.mu1[r], st.mu2[r], st.z[r], A0.x, A0.y);
+      accumulate<v>(Ere, Eim, Ore, Oim, st.mu2, st.mu1, b.x, b.y);
+#pragma unroll
+      for (int r = 0; r < R; ++r) step_pair(st.mu1[r], st.mu2[r], st.z[r], A1.x, A1.y);
+      accumulate<v + 2>(Ere, Eim, Ore, Oim, st.mu2, st.mu1, b.x, b.y);
     };
     step(std::integral_constant<int, 0>());
     step(std::integral_constant<int, 4>());
@@ -523,7 +448,7 @@ __device__ __forceinline__ void synthesis_item(const PlanDev& P, const Leg64Dev&
     const int q = blk * (LANES * R) + r * LANES + lane;
     if (q < nact)
       *reinterpret_cast<double4*>(Fm + (size_t)q * pstride) =
-          make_double4(Ere[r], Eim[r], z[r] * Ore[r], z[r] * Oim[r]);
+          make_double4(Ere[r], Eim[r], Ore[r], Oim[r]);
   }
   wave_sync();   // the next item's tile 0 is written after this one's last reads
 }
@@ -539,12 +464,7 @@ __global__ void __launch_bounds__(FP64_SYN_WAVES * LANES) legendre_synthesis_f64
   double* sA = leg64_lds + 2 + wave * LTILE;
   for (ItemQueue q(L.syn, leg64_lds); q.next(lane);) {
     const int k = q.k;
-    const Item64 it = L.syn.items[k];
-    switch (block_form(P, it.blk, LANES * R)) {
-      case EQ: synthesis_item<R, EQ>(P, L, k, it, blockIdx.y, lane, sA, bcoef, F); break;
-      case CAP: synthesis_item<R, CAP>(P, L, k, it, blockIdx.y, lane, sA, bcoef, F); break;
-      default: synthesis_item<R, MID>(P, L, k, it, blockIdx.y, lane, sA, bcoef, F);
-    }
+    synthesis_item<R>(P, L, k, L.syn.items[k], blockIdx.y, lane, sA, bcoef, F);
   }
 }
 
@@ -586,35 +506,29 @@ __global__ void reach_kernel(PlanDev P, uint16_t* __restrict__ wake, uint16_t* _
 // Plan time: the recurrence state of every ring pair of every item at its first l (workgroup k:
 // item k, thread t: pair t of the block), run with the kernels' own steps and scale checks (ch
 // values of l per check; items start at multiples of it).
-__global__ void start_state_kernel(PlanDev P, Leg64Dev L, const Item64* __restrict__ items, int ch,
+__global__ void start_state_kernel(PlanDev P, const Item64* __restrict__ items, int ch,
                                    double2* __restrict__ state, uint8_t* __restrict__ scale) {
   const Item64 it = items[blockIdx.x];
   const int m = it.m, rb = blockDim.x, q = it.blk * rb + threadIdx.x;
   const size_t at = (size_t)blockIdx.x * rb + threadIdx.x;
-  double u1 = 0.0, u2 = 0.0;
+  double mu1 = 0.0, mu2 = 0.0;   // mu_{m-1}; with A_mm = 0 the first step yields mu_m = -mu2
   int s = 0;
   if (q < P.n_active[m]) {
-    const int form = block_form(P, it.blk, rb);
     const RingPair rp = P.pairs[q];
     double v;
     sectoral_seed(m, rp.sin_t, P.norm_m[m], &v, &s);
-    u2 = form == MID ? -v : v;     // with zero coefficients in slot 0 the first step yields u_0 = v
-    const double zz = form == CAP ? (1.0 - rp.z) * (1.0 + rp.z) : rp.z * rp.z;
-    const double2* ab = reinterpret_cast<const double2*>(L.ab[form] + P.row_off[m]);
-    auto none = [](int, double) {};
+    mu2 = -v;
+    const double* Arow = P.A + P.row_off[m];
     for (int i = 0; i < it.i0; i += ch) {
-      for (int j = i / 2; j < (i + ch) / 2; j += 2) {
-        if (form == MID) step_pair<MID>(u1, u2, zz, ab[j], ab[j + 1], none);
-        else step_pair<CAP>(u1, u2, zz, ab[j], ab[j + 1], none);   // (EQ differs in the sign handed out)
-      }
-      if (s > 0 && fmax(fabs(u1), fabs(u2)) > BIG_THRESH) {
-        u1 *= RESCALE;
-        u2 *= RESCALE;
+      for (int j = i; j < i + ch; j += 2) step_pair(mu1, mu2, rp.z, Arow[j], Arow[j + 1]);
+      if (s > 0 && fmax(fabs(mu1), fabs(mu2)) > BIG_THRESH) {
+        mu1 *= RESCALE;
+        mu2 *= RESCALE;
         s -= 1;
       }
     }
   }
-  state[at] = make_double2(u1, u2);
+  state[at] = make_double2(mu1, mu2);
   scale[at] = (uint8_t)s;
 }
 
@@ -648,8 +562,8 @@ hipError_t launch_legendre_analysis_f64(const PlanDev& P, const Leg64Dev& L, int
 }
 
 hipError_t launch_legendre_coeff(const PlanDev& P, const Leg64Dev& L, const SynthArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(legendre_coeff_kernel, dim3((unsigned)((P.rows_total + COEFF_ROWS - 1) / COEFF_ROWS), a.nmaps),
-                     dim3(COEFF_WG), 0, s, P, L, a);
+  hipLaunchKernelGGL(legendre_coeff_kernel, dim3((unsigned)((P.rows_total + 255) / 256), a.nmaps), dim3(256), 0, s, P, L,
+                     a);
   return hipGetLastError();
 }
 
@@ -668,9 +582,9 @@ hipError_t launch_reach(const PlanDev& P, uint16_t* wake, uint16_t* rise, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_start_state(const PlanDev& P, const Leg64Dev& L, const Leg64List& T, int nitems, int ch,
+hipError_t launch_start_state(const PlanDev& P, const Leg64List& T, int nitems, int ch,
                               double2* state, uint8_t* scale, hipStream_t s) {
-  hipLaunchKernelGGL(start_state_kernel, dim3(nitems), dim3(T.rb), 0, s, P, L, T.items, ch, state, scale);
+  hipLaunchKernelGGL(start_state_kernel, dim3(nitems), dim3(T.rb), 0, s, P, T.items, ch, state, scale);
   return hipGetLastError();
 }
 

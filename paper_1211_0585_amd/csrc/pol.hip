@@ -376,57 +376,40 @@ __global__ void __launch_bounds__(S2_WAVES * LANES) spin2_synthesis_kernel(PlanD
   }
 }
 
-// One thread per (l, m, map) over the padded rows of the recurrence tables, on the flat grid with
-// two halo rows on either side that the spin-0 coefficient kernel has (i = l - m, P_i the sums
-// of the T blocks, alpha and beta the factors of the two-step recurrence):
-//   a_T = alpha_i P_i + beta_i P_{i-2},  a_E = -(K/2) sum partial_E,  a_B = (K/2) sum partial_B
+// One thread per (l, m, map) over the padded rows of the recurrence tables, on the flat grid
+// of the spin-0 coefficient kernel:
+//   a_T = C_l sum partial_T,  a_E = -(K/2) sum partial_E,  a_B = (K/2) sum partial_B
 //   SY_FROM_PARTIAL: s = F_l a with F_l = C_l (C_l + lambda tau Omega)^-1 (TE-coupled),
-//   SY_ALM_ONLY: s = a,  SY_FROM_ALM: s = the caller's alm (imaginary part dropped at m = 0),
-// and bcoef_t = alpha_i s_T,i + beta_{i+2} s_T,i+2.
+//   SY_ALM_ONLY: s = a,  SY_FROM_ALM: s = the caller's alm (imaginary part dropped at m = 0).
 // F_l in closed form for the TE block [[TT, TE], [TE, EE]] (mu = lambda tau Omega,
 // det = TT EE - TE^2, D = det + mu (TT + EE) + mu^2):
 //   F_TT = (det + TT mu) / D, F_TE = TE mu / D, F_EE = (det + EE mu) / D, F_BB = BB / (BB + mu)
 // (no cancellation, and 0 where the spectra vanish).
-constexpr int PC_WG = 256, PC_ROWS = PC_WG - 4;
+constexpr int PC_WG = 256;
 
 __global__ void __launch_bounds__(PC_WG) pol_coeff_kernel(PlanDev P, Leg64Dev L, Spin2Dev S2, PolCoeffArgs a) {
-  __shared__ double2 sP[PC_WG], sS[PC_WG];
-  const int t = threadIdx.x;
-  const int64_t r = (int64_t)blockIdx.x * PC_ROWS + t - 2;
+  const int64_t r = (int64_t)blockIdx.x * PC_WG + threadIdx.x;
+  if (r >= P.rows_total) return;
   const int map = blockIdx.y;
-  const bool own = t >= 2 && t < 2 + PC_ROWS && r < P.rows_total;
   const int lmax = P.lmax;
   const double mu = a.lambda * P.tau * P.omega;
-  int m = 0, i = 0;
-  bool val = false;
-  double2 co = make_double2(0.0, 0.0);
-  double K = 0.0;
-  if (r >= 0 && r < P.rows_total) {
-    m = P.row_m[r];
-    i = (int)(r - P.row_off[m]);
-    val = i < lmax - m + 1;
-    if (val) {
-      co = L.co[r];
-      K = S2.K[r];
-    }
-  }
-  const int l = m + i;
-  const int64_t at = alm_index(lmax, m, m) + i;
+  const int m = P.row_m[r];
+  const int i = (int)(r - P.row_off[m]);
   double2 sT = make_double2(0, 0), sE = sT, sB = sT;
-  if (a.mode == SY_FROM_ALM) {
-    if (val) {
+  double K = 0.0, C0 = 0.0;
+  if (i < lmax - m + 1) {
+    const int l = m + i;
+    const int64_t at = alm_index(lmax, m, m) + i;
+    K = S2.K[r];
+    C0 = P.C[r];
+    if (a.mode == SY_FROM_ALM) {
       const double2* al = a.alm_in + (size_t)map * 3 * P.nalm + at;
       sT = al[0];
       sE = al[P.nalm];
       sB = al[2 * P.nalm];
       if (m == 0) sT.y = sE.y = sB.y = 0.0;
-    }
-  } else {
-    double2 p = make_double2(0, 0);
-    if (val) p = block_partials(P, L, a.partial_t + (size_t)map * P.nblk_max * P.nalm + at, m, i);
-    sP[t] = p;
-    __syncthreads();
-    if (val && t >= 2) {
+    } else {
+      const double2 p = block_partials(P, L, a.partial_t + (size_t)map * P.nblk_max * P.nalm + at, m, i);
       const int nbe = a.nblk2_m[m];
       double er = 0, ei = 0, br = 0, bi = 0;
       for (int k = 0; k < nbe; ++k) {
@@ -436,12 +419,7 @@ __global__ void __launch_bounds__(PC_WG) pol_coeff_kernel(PlanDev P, Leg64Dev L,
         br += e.z;
         bi += e.w;
       }
-      sT = make_double2(co.x * p.x, co.x * p.y);
-      if (co.y != 0.0) {
-        const double2 q = sP[t - 2];
-        sT.x = fma(co.y, q.x, sT.x);
-        sT.y = fma(co.y, q.y, sT.y);
-      }
+      sT = make_double2(p.x * C0, p.y * C0);
       sE = make_double2(-0.5 * K * er, -0.5 * K * ei);
       sB = make_double2(0.5 * K * br, 0.5 * K * bi);
       if (a.mode == SY_FROM_PARTIAL) {
@@ -458,29 +436,18 @@ __global__ void __launch_bounds__(PC_WG) pol_coeff_kernel(PlanDev P, Leg64Dev L,
         sB = make_double2(fbb * sB.x, fbb * sB.y);
       }
     }
-  }
-  if (own && val && a.alm_out) {
-    double2* ao = a.alm_out + (size_t)map * 3 * P.nalm + at;
-    ao[0] = sT;
-    ao[P.nalm] = sE;
-    ao[2 * P.nalm] = sB;
+    if (a.alm_out) {
+      double2* ao = a.alm_out + (size_t)map * 3 * P.nalm + at;
+      ao[0] = sT;
+      ao[P.nalm] = sE;
+      ao[2 * P.nalm] = sB;
+    }
   }
   if (a.mode != SY_ALM_ONLY) {
-    sS[t] = sT;
-    __syncthreads();
-    if (own) {
-      double2 b = make_double2(co.x * sT.x, co.x * sT.y);
-      const double beta = val ? L.co[r + 2].y : 0.0;   // (a row ends in padding: r + 2 stays inside it)
-      if (beta != 0.0) {
-        const double2 n = sS[t + 2];
-        b.x = fma(beta, n.x, b.x);
-        b.y = fma(beta, n.y, b.y);
-      }
-      a.bcoef_t[(size_t)map * P.rows_total + r] = b;
-      double2* be = a.bcoef_eb + ((size_t)map * P.rows_total + r) * 2;
-      be[0] = make_double2(-0.5 * K * sE.x, -0.5 * K * sE.y);
-      be[1] = make_double2(-0.5 * K * sB.x, -0.5 * K * sB.y);
-    }
+    a.bcoef_t[(size_t)map * P.rows_total + r] = make_double2(sT.x * C0, sT.y * C0);
+    double2* be = a.bcoef_eb + ((size_t)map * P.rows_total + r) * 2;
+    be[0] = make_double2(-0.5 * K * sE.x, -0.5 * K * sE.y);
+    be[1] = make_double2(-0.5 * K * sB.x, -0.5 * K * sB.y);
   }
 }
 
@@ -503,7 +470,7 @@ hipError_t launch_spin2_synthesis(const PlanDev& P, const Spin2Dev& S2, int nmap
 
 hipError_t launch_pol_coeff(const PlanDev& P, const Leg64Dev& L, const Spin2Dev& S2, const PolCoeffArgs& a,
                             hipStream_t s) {
-  hipLaunchKernelGGL(pol_coeff_kernel, dim3((unsigned)((P.rows_total + PC_ROWS - 1) / PC_ROWS), a.nmaps), dim3(PC_WG), 0,
+  hipLaunchKernelGGL(pol_coeff_kernel, dim3((unsigned)((P.rows_total + PC_WG - 1) / PC_WG), a.nmaps), dim3(PC_WG), 0,
                      s, P, L, S2, a);
   return hipGetLastError();
 }
