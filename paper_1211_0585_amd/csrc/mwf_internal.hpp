@@ -84,6 +84,17 @@ constexpr int FP64_SCALED_COST_SYN = 6;
 constexpr int FP64_ITEM_COST_L = 16;
 constexpr uint16_t WAKE_NEVER = 0xffff;
 
+// x * 2^e as v * 2^(-512 s) with |v| >= 2^-449 when s = 0.
+__host__ __device__ __forceinline__ void split_scale(double x, int e, double* v, int* s) {
+  int t;
+  x = frexp(x, &t);
+  e += t;
+  int sc = 0;
+  if (e < 64 - SCALE_BITS) sc = (64 - SCALE_BITS - e + SCALE_BITS - 1) / SCALE_BITS;
+  *v = ldexp(x, e + SCALE_BITS * sc);
+  *s = sc;
+}
+
 // lambda_mm(z) = norm_m sin^m(theta) as v * 2^(-512 s) with |v| >= 2^-449 when s = 0.
 __device__ __forceinline__ void sectoral_seed(int m, double sin_t, double norm, double* v, int* s) {
   int eb;
@@ -104,13 +115,45 @@ __device__ __forceinline__ void sectoral_seed(int m, double sin_t, double norm, 
       eb = 2 * eb + t;
     }
   }
-  int t;
-  double x = frexp(norm * r, &t);
-  const int e = er + t;                 // value = x * 2^e, 0.5 <= |x| < 1
-  int sc = 0;
-  if (e < 64 - SCALE_BITS) sc = (64 - SCALE_BITS - e + SCALE_BITS - 1) / SCALE_BITS;
-  *v = ldexp(x, e + SCALE_BITS * sc);
-  *s = sc;
+  split_scale(norm * r, er, v, s);
+}
+
+// The same to the last bits, for the FP64 start states (plan time): sectoral_seed raises a rounded
+// sin(theta) to the power m, which costs up to m / 2 roundings (4e-14 of a ring's norm at Nside 512
+// next to the equator, where the recurrence itself keeps 1e-15). Here sin^2 = 1 - z^2 of the
+// given z is carried as an unevaluated sum of two doubles through the powers.
+__host__ __device__ __forceinline__ void sectoral_seed_full(int m, double z, double norm, double* v, int* s) {
+#pragma clang fp contract(off)   // the differences below are the roundings of these very products and sums
+  struct Two {
+    double h, l;
+    int e;      // (h + l) 2^e, 0.5 <= |h| < 1
+  };
+  auto normal = [](double h, double l, int e) {
+#pragma clang fp contract(off)
+    const double sum = h + l;
+    l -= sum - h;
+    int t;
+    const double f = frexp(sum, &t);
+    return Two{f, ldexp(l, -t), e + t};
+  };
+  auto mul = [&](const Two& a, const Two& b) {
+#pragma clang fp contract(off)
+    const double p = a.h * b.h;
+    return normal(p, fma(a.h, b.l, fma(a.l, b.h, fma(a.h, b.h, -p))), a.e + b.e);
+  };
+  const double p = z * z, d = 1.0 - p;
+  Two b = normal(d, ((1.0 - d) - p) - fma(z, z, -p), 0);   // sin^2
+  Two r{0.5, 0.0, 1};
+  if (m & 1) {                                             // sin
+    const int odd = b.e & 1;
+    const double h = odd ? 2.0 * b.h : b.h, l = odd ? 2.0 * b.l : b.l, q = sqrt(h);
+    r = normal(q, (fma(-q, q, h) + l) / (2.0 * q), (b.e - odd) / 2);
+  }
+  for (int k = m / 2; k; k >>= 1) {
+    if (k & 1) r = mul(r, b);
+    if (k > 1) b = mul(b, b);
+  }
+  split_scale(fma(norm, r.l, norm * r.h), r.e, v, s);
 }
 
 // Work item of the m-parallel phase: one m and one block of ring pairs.

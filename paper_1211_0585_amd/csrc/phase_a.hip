@@ -516,7 +516,7 @@ __global__ void start_state_kernel(PlanDev P, const Item64* __restrict__ items, 
   if (q < P.n_active[m]) {
     const RingPair rp = P.pairs[q];
     double v;
-    sectoral_seed(m, rp.sin_t, P.norm_m[m], &v, &s);
+    sectoral_seed_full(m, rp.z, P.norm_m[m], &v, &s);
     mu2 = -v;
     const double* Arow = P.A + P.row_off[m];
     for (int i = 0; i < it.i0; i += ch) {

@@ -54,7 +54,8 @@ def phases(nside, rings, lmax):
     return np.cos(a) + 1j * np.sin(a)
 
 
-SHAPES = [(128, 511, [0], 1.2e-14), (128, 511, [255], 2.8e-13), (512, 1024, [0], 1.2e-14), (1024, 2048, [0], 1.2e-14)]
+SHAPES = [(128, 511, [0, 1, 4, 16, 64, 128], 1.2e-14), (128, 511, [255], 2.8e-13),
+          (512, 1024, [0, 1, 2, 4, 16, 64, 256, 512], 1.2e-14), (1024, 2048, [0, 1, 4, 64, 256, 1024], 1.2e-14)]
 
 
 @pytest.mark.parametrize("nside,lmax,pairs,bar", SHAPES)
