@@ -122,9 +122,11 @@ size_t geometry_bytes(int nside, int lmax, bool fp64) {
       blue += M + 4 * i;
     }
   // FP64 Legendre work lists: a start state per ring pair of every work item (at
-  // most one analysis item per (m, block) and 32 l, two per wave of a full launch beyond that)
-  const size_t items = std::min<size_t>(5 * nalm / 16, (size_t)(lmax + 1) * ((nside + 127) / 128) + 8192) +
-                       (size_t)(lmax + 1) * ((nside + 127) / 128);
+  // most one analysis item per (m, block) and 32 l, two per wave of a full launch beyond that; as many
+  // again for batches where one map's items are short)
+  const size_t nblk = (nside + 127) / 128, blocks = (size_t)(lmax + 1) * nblk;
+  const size_t ana = std::min<size_t>(5 * nalm / 16, blocks + 8192);
+  const size_t items = (nalm * nblk < (size_t)2 * FP64_BATCH_PART * 6144 ? 2 : 1) * ana + blocks;
   const size_t leg64 = fp64 ? items * std::min(2 * nside + 63, 256) * 17 : 0;
   return 2 * rows * 8 + blue * 24 + (size_t)(lmax + 1) * 64 + (size_t)(16 * nside + 64) * 24 +
          5 * nalm + leg64 + 256 * 1024;

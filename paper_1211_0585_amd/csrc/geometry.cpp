@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <complex>
 #include <map>
@@ -407,18 +408,23 @@ int build_geometry(Geometry& g) {
   return WF_OK;
 }
 
-// Packs items (with their costs) into the workgroups of a launch, one per CU: items, most costly
-// first, each go to the least-loaded workgroup, which keeps that order. Small lists take as
-// many waves per workgroup as give every CU work. off: the item range of each workgroup.
+// Workgroups and waves of a launch of one map: one workgroup per CU, of as many waves as give every
+// CU work where items are few.
+void one_map_shape(size_t items, int n_cu, int max_waves, int* nwg, int* waves) {
+  int W = 1;
+  while (W < max_waves && (int64_t)W * n_cu < (int64_t)items) W = std::min(2 * W, max_waves);
+  *waves = W;
+  *nwg = std::max(1, std::min(n_cu, (int)((items + W - 1) / W)));
+}
+
+// Packs items (with their costs) into nwg workgroups: items, most costly first, each go to the
+// least-loaded workgroup, which keeps that order. off: the item range of each workgroup.
 // In a full launch the items of eight consecutive m go to the workgroups of one XCD (workgroup b
 // runs on XCD b mod 8): their 32-byte entries of G and F share 128-byte lines, which then are
 // fetched into one L2 and written back from one (Nside 512: analysis 107 -> 102 us, synthesis
 // 75 -> 69 us).
-std::vector<Item64> pack_items(const std::vector<Item64>& items, const std::vector<int64_t>& cost, int n_cu,
-                               int max_waves, std::vector<int32_t>* off, int* waves) {
-  int W = 1;
-  while (W < max_waves && (int64_t)W * n_cu < (int64_t)items.size()) W = std::min(2 * W, max_waves);
-  const int nwg = std::max(1, std::min(n_cu, (int)((items.size() + W - 1) / W)));
+std::vector<Item64> pack_items(const std::vector<Item64>& items, const std::vector<int64_t>& cost, int nwg,
+                               std::vector<int32_t>* off) {
   const int nx = nwg % 8 == 0 && nwg >= 64 ? 8 : 1;
   // least-loaded dealing of ids (in the order given, with their loads) to n places
   auto deal = [](const std::vector<int>& ids, const std::vector<int64_t>& load, int n) {
@@ -462,7 +468,6 @@ std::vector<Item64> pack_items(const std::vector<Item64>& items, const std::vect
     for (int i : to[b % nx][b / nx]) packed.push_back(items[i]);
     off->push_back((int32_t)packed.size());
   }
-  *waves = W;
   return packed;
 }
 
@@ -496,18 +501,21 @@ int build_leg64(Geometry& g) {
     return 4 * (n - sc) + scaled_cost * sc + 4 * FP64_ITEM_COST_L;
   };
   const auto whole = blocks(g.ring_block_ana);
-  // analysis: the l of a block in parts of about half a wave's share, 32 at least (in chunks of 16)
   std::vector<int32_t> start((size_t)(lmax + 1) * nbm);
+  for (int m = 0; m <= lmax; ++m)
+    for (int b = 0; b < nbm; ++b) start[(size_t)m * nbm + b] = lmax - m + 1;
+  int64_t total = 0;
+  for (const Block& b : whole) {
+    start[(size_t)b.m * nbm + b.blk] = b.first;
+    total += lmax - b.m + 1 - b.first;
+  }
   std::vector<Item64> items;
   std::vector<int64_t> cost;
-  {
-    for (int m = 0; m <= lmax; ++m)
-      for (int b = 0; b < nbm; ++b) start[(size_t)m * nbm + b] = lmax - m + 1;
-    int64_t total = 0;
-    for (const Block& b : whole) total += lmax - b.m + 1 - b.first;
-    const int64_t part = std::max<int64_t>(32, (total / (2 * FP64_ANA_WAVES * g.n_cu) + CHUNK - 1) / CHUNK * CHUNK);
+  // analysis items: the l of a block in parts of about `part` (in chunks of 16)
+  auto split = [&](int64_t part) {
+    items.clear();
+    cost.clear();
     for (const Block& b : whole) {
-      start[(size_t)b.m * nbm + b.blk] = b.first;
       const int nl = lmax - b.m + 1, n = nl - b.first;
       if (n == 0) continue;
       const int parts = std::max(1, (int)((n + part / 2) / part));
@@ -518,10 +526,32 @@ int build_leg64(Geometry& g) {
         cost.push_back(item_cost(w, b.scaled, FP64_SCALED_COST_ANA));
       }
     }
+  };
+  std::vector<int32_t> wg_ana, wg_batch, wg_syn;
+  int nwg = 1, waves_ana = 1, waves_syn = 1;
+  // few maps: parts of about half a wave's share of one map, 32 at least
+  const int64_t part = std::max<int64_t>(32, (total / (2 * FP64_ANA_WAVES * g.n_cu) + CHUNK - 1) / CHUNK * CHUNK);
+  split(part);
+  one_map_shape(items.size(), g.n_cu, FP64_ANA_WAVES, &nwg, &waves_ana);
+  const auto ia = pack_items(items, cost, nwg, &wg_ana);
+  // Where these are short, the set-up of an item (ring states and S/D, 256 rows of G apart) is half of
+  // its time, which pays only while waves would idle otherwise: batches take longer ones, in small
+  // workgroups of two items a wave. Analysis of 3, 8, 16 and 48 maps (us) with the items of one
+  // map and with these: Nside 256, lmax 300 41, 94, 179, 490 and 32, 58, 101, 274; Nside 256, lmax
+  // 512 64, 158, 325, 971 and 63, 131, 258, 742; Nside 128, lmax 256 18, 33, 56, 152 and 22, 31, 51, 120; Nside
+  // 64, lmax 128 8, 11, 16, 33 and 11, 13, 17, 31. From that the rule: two maps, and 80 l a
+  // wave of a full launch. One map of more than FP64_BATCH_PART l per item has items as long already.
+  std::vector<Item64> ib;
+  int batch_from = INT_MAX;
+  if (part < FP64_BATCH_PART) {
+    split(FP64_BATCH_PART);
+    const int per_wg = 2 * FP64_BATCH_WAVES;
+    nwg = std::max(1, (int)((items.size() + per_wg - 1) / per_wg));
+    if (nwg > 8) nwg = (nwg + 7) / 8 * 8;
+    ib = pack_items(items, cost, nwg, &wg_batch);
+    const int64_t from = ((int64_t)80 * FP64_ANA_WAVES * g.n_cu + total - 1) / std::max<int64_t>(total, 1);
+    batch_from = (int)std::min<int64_t>(std::max<int64_t>(from, 2), INT_MAX);
   }
-  std::vector<int32_t> wg_ana, wg_syn;
-  int waves_ana = 1, waves_syn = 1;
-  const auto ia = pack_items(items, cost, g.n_cu, FP64_ANA_WAVES, &wg_ana, &waves_ana);
   // synthesis: the largest blocks, up to 256 pairs, that still give every wave of a full launch an
   // item and a half (a wave's share is then not set by its longest item). A smaller block that
   // never rises inside one of the analysis's that does gets an item of no steps, which writes
@@ -541,7 +571,8 @@ int build_leg64(Geometry& g) {
     }
     if (rb_syn == LANES || (int64_t)items.size() * 2 >= (int64_t)FP64_SYN_WAVES * g.n_cu * 3) break;
   }
-  const auto is = pack_items(items, cost, g.n_cu, FP64_SYN_WAVES, &wg_syn, &waves_syn);
+  one_map_shape(items.size(), g.n_cu, FP64_SYN_WAVES, &nwg, &waves_syn);
+  const auto is = pack_items(items, cost, nwg, &wg_syn);
   std::vector<double> z(g.npairs);
   for (int q = 0; q < g.npairs; ++q) z[q] = ring_geometry(g.nside, 2 * g.nside - q).z;
 
@@ -585,6 +616,8 @@ int build_leg64(Geometry& g) {
   if ((rc = make_list(L.ana, ia, wg_ana, waves_ana, g.ring_block_ana)) ||
       (rc = make_list(L.syn, is, wg_syn, waves_syn, rb_syn)))
     return rc;
+  L.batch_from = batch_from;
+  if (!ib.empty() && (rc = make_list(L.ana_batch, ib, wg_batch, FP64_BATCH_WAVES, g.ring_block_ana))) return rc;
   MWF_HIP(hipStreamSynchronize(nullptr));
   g.leg64 = L;
   g.leg64_ready = true;

@@ -79,6 +79,9 @@ constexpr int LANES = 64;            // wavefront width on CDNA
 // synthesis), and 4 FP64_ITEM_COST_L for its set-up. (Weights from timing the kernels.)
 constexpr int FP64_ANA_WAVES = 12;
 constexpr int FP64_SYN_WAVES = 16;
+// Analysis of a batch: waves per workgroup and least l per item (see build_leg64).
+constexpr int FP64_BATCH_WAVES = 4;
+constexpr int FP64_BATCH_PART = 96;
 constexpr int FP64_SCALED_COST_ANA = 5;
 constexpr int FP64_SCALED_COST_SYN = 6;
 constexpr int FP64_ITEM_COST_L = 16;
@@ -213,6 +216,8 @@ struct Leg64Dev {
   const double* z;         // [npairs] z of the north ring
   const int32_t* start;    // [lmax+1][nblk_max] first l - m summed by the analysis in each block
   Leg64List ana, syn;
+  Leg64List ana_batch;     // analysis of batch_from maps and more
+  int32_t batch_from, pad_;
 };
 
 // Sum of the analysis blocks' partial sums of one (l, m), i = l - m (FP64), pb at block 0: KB at

@@ -40,11 +40,13 @@
 // 2^-128 (m well above l sin(theta)) are not generated, summed or written at all (12 to 20 %
 // of the steps). The analysis splits a block's l into several items, since their outputs are
 // independent: with one item per (m, block) at Nside 512, 3500 items for 3072 waves, the
-// longest set the launch's time (1.67 of the mean). The synthesis sums over l and takes smaller
+// longest set the launch's time (1.67 of the mean). A batch, whose maps fill the chip together, takes
+// longer items where one map's are short. The synthesis sums over l and takes smaller
 // blocks instead where there are few items.
 //
-// A launch is one workgroup per CU of up to 12 (analysis) or 16 waves. The items are balanced over
-// the workgroups at plan time; inside one the waves take them from a shared queue.
+// A launch is one workgroup per CU (and map) of up to 12 (analysis) or 16 waves, for such a batch
+// more of four. The items are balanced over the workgroups at plan time; inside one the waves take them
+// from a shared queue.
 //
 // The recurrence coefficients are fetched 64 values of l ahead with one vector load and read
 // from LDS; the synthesis coefficients, twice as many, are held 16 to a row of lanes and
@@ -551,8 +553,10 @@ hipError_t launch_syn_r(const PlanDev& P, const Leg64Dev& L, const SynthArgs& a,
 
 }  // namespace
 
-hipError_t launch_legendre_analysis_f64(const PlanDev& P, const Leg64Dev& L, int nmaps, const double* G,
+hipError_t launch_legendre_analysis_f64(const PlanDev& P, const Leg64Dev& lists, int nmaps, const double* G,
                                         double2* partial, hipStream_t s) {
+  Leg64Dev L = lists;
+  if (nmaps >= L.batch_from) L.ana = L.ana_batch;
   switch (L.ana.rb / LANES) {
     case 1: return launch_ana_r<1>(P, L, nmaps, G, partial, s);
     case 2: return launch_ana_r<2>(P, L, nmaps, G, partial, s);
