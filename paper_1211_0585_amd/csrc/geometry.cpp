@@ -60,8 +60,13 @@ std::mutex g_geo_mu;
 // Weak entries: the tables of a shape live while a plan or serving lane holds them.
 std::map<std::tuple<int, int, int>, std::weak_ptr<Geometry>> g_geo;
 
-// Runs the reach kernel of a geometry whose recurrence tables are on the device (see launch_reach).
-int run_reach(const Geometry& g, std::vector<uint16_t>* wake, std::vector<uint16_t>* rise) {
+// Per (m, ring pair), what launch_reach gives; rise is empty where it was not asked for.
+struct Reach {
+  std::vector<uint16_t> wake, rise;
+};
+
+// Runs the reach kernel of a geometry whose recurrence tables are on the device.
+int run_reach(const Geometry& g, bool rise, Reach* out) {
   PlanDev D{};
   D.nside = g.nside;
   D.lmax = g.lmax;
@@ -74,15 +79,13 @@ int run_reach(const Geometry& g, std::vector<uint16_t>* wake, std::vector<uint16
   uint16_t *dw = nullptr, *dr = nullptr;
   DevMem tmp;
   int rc;
-  if ((rc = tmp.alloc(&dw, n)) || (rc = tmp.alloc(&dr, n))) return rc;
+  if ((rc = tmp.alloc(&dw, n)) || (rise && (rc = tmp.alloc(&dr, n)))) return rc;
   MWF_HIP(launch_reach(D, dw, dr, nullptr));
-  if (wake) {
-    wake->resize(n);
-    MWF_HIP(hipMemcpy(wake->data(), dw, n * sizeof(uint16_t), hipMemcpyDeviceToHost));
-  }
+  out->wake.resize(n);
+  MWF_HIP(hipMemcpy(out->wake.data(), dw, n * sizeof(uint16_t), hipMemcpyDeviceToHost));
   if (rise) {
-    rise->resize(n);
-    MWF_HIP(hipMemcpy(rise->data(), dr, n * sizeof(uint16_t), hipMemcpyDeviceToHost));
+    out->rise.resize(n);
+    MWF_HIP(hipMemcpy(out->rise.data(), dr, n * sizeof(uint16_t), hipMemcpyDeviceToHost));
   }
   return WF_OK;
 }
@@ -106,7 +109,8 @@ std::vector<WorkItem> items_by_size(const Geometry& g, int rb) {
   return items;
 }
 
-int build_geometry(Geometry& g) {
+// reach receives the polar reach of every (m, ring pair), with the rises for an FP64 plan.
+int build_geometry(Geometry& g, bool fp64, Reach* reach) {
   const int nside = g.nside, lmax = g.lmax;
   g.npix = 12LL * nside * nside;
   g.nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
@@ -350,8 +354,8 @@ int build_geometry(Geometry& g) {
 
   // ---- polar skip: ring pairs whose lambda_lm never leaves the negligible range
   {
-    std::vector<uint16_t> wake;
-    if ((rc = run_reach(g, &wake, nullptr))) return rc;
+    if ((rc = run_reach(g, fp64, reach))) return rc;
+    const std::vector<uint16_t>& wake = reach->wake;
     g.n_active.assign(lmax + 1, 0);
     g.units_active = 0;
     for (int m = 0; m <= lmax; ++m) {
@@ -472,12 +476,11 @@ std::vector<Item64> pack_items(const std::vector<Item64>& items, const std::vect
 }
 
 // Work lists of the FP64 Legendre kernels (Leg64Dev), made for the first FP64 plan of the shape.
-int build_leg64(Geometry& g) {
+int build_leg64(Geometry& g, const Reach& reach) {
   const int lmax = g.lmax, nbm = g.nblk_max_ana;
   // (m, block of rb pairs) with the first l - m, in chunks of 16, at which a ring pair of it exceeds
   // 2^-128, and the l - m up to which a ring of it is still scaled
-  std::vector<uint16_t> wake, rise;
-  if (int rc = run_reach(g, &wake, &rise)) return rc;
+  const std::vector<uint16_t>&wake = reach.wake, &rise = reach.rise;
   struct Block {
     int m, blk, first, scaled;
   };
@@ -660,8 +663,11 @@ int get_geometry(int nside, int lmax, bool fp64, std::shared_ptr<Geometry>* out)
   auto it = g_geo.find(key);
   if (it != g_geo.end()) {
     if (auto live = it->second.lock()) {
-      if (fp64 && !live->leg64_ready)
-        if (int rc = build_leg64(*live)) return rc;
+      if (fp64 && !live->leg64_ready) {
+        Reach reach;
+        if (int rc = run_reach(*live, true, &reach)) return rc;
+        if (int rc = build_leg64(*live, reach)) return rc;
+      }
       *out = live;
       return WF_OK;
     }
@@ -672,8 +678,9 @@ int get_geometry(int nside, int lmax, bool fp64, std::shared_ptr<Geometry>* out)
   if (g->n_cu <= 0) g->n_cu = 1;
   g->nside = nside;
   g->lmax = lmax;
-  int rc = build_geometry(*g);
-  if (!rc && fp64) rc = build_leg64(*g);
+  Reach reach;
+  int rc = build_geometry(*g, fp64, &reach);
+  if (!rc && fp64) rc = build_leg64(*g, reach);
   if (rc) return rc;
   g_geo[key] = g;
   *out = g;

@@ -623,7 +623,7 @@ hipError_t launch_spin2_synthesis(const PlanDev& P, const Spin2Dev& S2, int nmap
                                   hipStream_t s);
 
 // Plan-time, per (m, ring pair): where lambda_lm leaves the scaled range and where it exceeds
-// 2^-128, or WAKE_NEVER (polar skip, start and cost of the FP64 work items).
+// 2^-128, or WAKE_NEVER (polar skip, start and cost of the FP64 work items; rise may be null).
 hipError_t launch_reach(const PlanDev& P, uint16_t* wake, uint16_t* rise, hipStream_t s);
 // Plan-time: state and scale of a work list, from its items.
 hipError_t launch_start_state(const PlanDev& P, const Leg64List& T, int nitems, int ch, double2* state, uint8_t* scale,

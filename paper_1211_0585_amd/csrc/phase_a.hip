@@ -473,7 +473,7 @@ __global__ void __launch_bounds__(FP64_SYN_WAVES * LANES) legendre_synthesis_f64
 // Plan time, per (m, ring pair): the first l - m + 1 at which lambda_lm(z_q) has
 // risen above the scaled range (its scale reached 0; 0 if it starts there), or
 // WAKE_NEVER if that does not happen for l <= lmax (the pair is skipped for m); and
-// likewise in `rise` the first l - m at which it exceeds 2^-128.
+// likewise in `rise`, unless that is null, the first l - m at which it exceeds 2^-128.
 __global__ void reach_kernel(PlanDev P, uint16_t* __restrict__ wake, uint16_t* __restrict__ rise) {
   const int m = blockIdx.y;
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
@@ -483,7 +483,7 @@ __global__ void reach_kernel(PlanDev P, uint16_t* __restrict__ wake, uint16_t* _
   int s;
   sectoral_seed(m, rp.sin_t, P.norm_m[m], &v, &s);
   uint16_t w = s == 0 ? 0 : WAKE_NEVER, e = s == 0 && fabs(v) > RISE_THRESH ? 0 : WAKE_NEVER;
-  if (e != 0) {
+  if (rise ? e != 0 : w != 0) {
     const double* Arow = P.A + P.row_off[m];
     double mu1 = 0.0, mu2 = -v;
     for (int l = m; l <= P.lmax; ++l) {
@@ -493,7 +493,10 @@ __global__ void reach_kernel(PlanDev P, uint16_t* __restrict__ wake, uint16_t* _
       if (s > 0 && fabs(mu1) > BIG_THRESH) {
         mu1 *= RESCALE;
         mu2 *= RESCALE;
-        if (--s == 0) w = (uint16_t)(l - m + 1);
+        if (--s == 0) {
+          w = (uint16_t)(l - m + 1);
+          if (!rise) break;
+        }
       }
       if (s == 0 && fabs(mu1) > RISE_THRESH) {
         e = (uint16_t)(l - m);
@@ -502,7 +505,7 @@ __global__ void reach_kernel(PlanDev P, uint16_t* __restrict__ wake, uint16_t* _
     }
   }
   wake[(size_t)m * P.npairs + q] = w;
-  rise[(size_t)m * P.npairs + q] = e;
+  if (rise) rise[(size_t)m * P.npairs + q] = e;
 }
 
 // Plan time: the recurrence state of every ring pair of every item at its first l (workgroup k:
