@@ -742,16 +742,18 @@ int band_plan(wf_plan_s* p, int L, wf_plan_s** out) {
   b->q = p->q;
   b->cl = p->cl;
   b->n_obs = p->n_obs;
-  // one second stream for the whole family of plans: each stream a process holds
-  // takes a share of the few hardware queues, also from unrelated work
-  if (int rc = ensure_aux(p)) {
-    delete b;
-    return rc;
+  // one second stream for the whole family of plans, where the ring phase of one map takes
+  // it: each stream a process holds takes a share of the few hardware queues, also from unrelated work
+  if (!geo->one_ring_launch(1)) {
+    if (int rc = ensure_aux(p)) {
+      delete b;
+      return rc;
+    }
+    b->aux = p->aux;
+    b->ev_fork = p->ev_fork;
+    b->ev_join = p->ev_join;
+    b->owns_aux = false;
   }
-  b->aux = p->aux;
-  b->ev_fork = p->ev_fork;
-  b->ev_join = p->ev_join;
-  b->owns_aux = false;
   if (int rc = plan_alloc(b)) {
     delete b;
     return rc;

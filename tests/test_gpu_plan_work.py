@@ -36,3 +36,18 @@ def test_one_reach_pass_per_new_shape():
     assert made(32, 43, 0, keep) == (0, 0)
     for p in keep:
         p.close()
+
+
+@pytest.mark.parametrize("nside,streams", [(16, 0), (256, 0), (1024, 1)])
+def test_truncated_solve_makes_a_stream_only_where_used(nside, streams):
+    """The ring phase of one map forks onto a second stream only where its transforms do not go in one
+    launch (beyond 4096 points); a truncated solve makes no stream anywhere else."""
+    import torch
+    from paper_1211_0585_amd import mwf
+    lmax, npix = 24, 12 * nside * nside
+    x = torch.randn(npix, dtype=torch.float64, device="cuda")
+    with mwf.Plan(nside, lmax, np.ones(lmax + 1), np.ones(npix)) as p:
+        names = events(lambda: p.solve_banded(x, [3.0, 2.0, 1.0], [8, 16, 24]))
+        p.sync()
+    assert sum("phase_b_kernel" in n for n in names) >= 4
+    assert sum("hipStreamCreate" in n for n in names) == streams
