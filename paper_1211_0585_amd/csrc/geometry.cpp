@@ -300,24 +300,6 @@ int build_geometry(Geometry& g, bool fp64, Reach* reach) {
         if ((rc = M.upload(&d, lists[k][c]))) return rc;
         g.ring_cls[k][c] = RingClass{d, (int32_t)lists[k][c].size(), lens[k][c]};
       }
-    // Bluestein rings of the longest transform apart from the shorter ones: at the
-    // longest length alone they can hold all of the chip's LDS. The mixed-radix rings go
-    // with the shorter ones at their own length: these two launches run only the plain
-    // ring kernel, whose transforms need n <= 4 MAXB NT, not the half-length bound of
-    // the class lists (with the longest ones, or at twice their length, they made the
-    // one-map ring phase 5 and 16 us slower).
-    std::vector<int32_t> bl[2];
-    int bl_len[2] = {4, 4};
-    for (int q : lists[0][0]) {
-      const int k = pairs[q].bl_M == lens[0][0] ? 0 : 1;
-      bl[k].push_back(q);
-      bl_len[k] = std::max(bl_len[k], pairs[q].mix ? pairs[q].nphi : class_len(pairs[q]));
-    }
-    for (int k = 0; k < 2; ++k) {
-      int32_t* d = nullptr;
-      if ((rc = M.upload(&d, bl[k]))) return rc;
-      g.blue_split[k] = RingClass{d, (int32_t)bl[k].size(), bl_len[k]};
-    }
     // All ring pairs in one list, longest transforms first, up to Nside 512 (at 1024 the FP64 buffer
     // of the longest leaves one workgroup a CU, and the other rings would take its size): one or a
     // few maps take one launch. The launches by kind, the event pair that forked and joined their
@@ -335,8 +317,27 @@ int build_geometry(Geometry& g, bool fp64, Reach* reach) {
       int32_t* d = nullptr;
       if ((rc = M.upload(&d, all))) return rc;
       g.ring_all = RingClass{d, g.npairs, len};
+    } else {
+      // Few maps otherwise: Bluestein rings of the longest transform apart from the shorter ones: at the
+      // longest length alone they can hold all of the chip's LDS. The mixed-radix rings go
+      // with the shorter ones at their own length: these two launches run only the plain
+      // ring kernel, whose transforms need n <= 4 MAXB NT, not the half-length bound of
+      // the class lists (with the longest ones, or at twice their length, they made the
+      // one-map ring phase 5 and 16 us slower).
+      std::vector<int32_t> bl[2];
+      int bl_len[2] = {4, 4};
+      for (int q : lists[0][0]) {
+        const int k = pairs[q].bl_M == lens[0][0] ? 0 : 1;
+        bl[k].push_back(q);
+        bl_len[k] = std::max(bl_len[k], pairs[q].mix ? pairs[q].nphi : class_len(pairs[q]));
+      }
+      for (int k = 0; k < 2; ++k) {
+        int32_t* d = nullptr;
+        if ((rc = M.upload(&d, bl[k]))) return rc;
+        g.blue_split[k] = RingClass{d, (int32_t)bl[k].size(), bl_len[k]};
+      }
     }
-    // the same split of the batched class 0: at 64 maps the 2048-point Bluestein rings and
+    // such a split of the batched class 0, whatever the size: at 64 maps the 2048-point Bluestein rings and
     // the long mixed-radix rings ran in the launch sized for the 4096-point ones
     std::vector<int32_t> ls[2];
     int ls_len[2] = {4, 4};
