@@ -580,7 +580,8 @@ int build_leg64(Geometry& g, const Reach& reach) {
   std::vector<double> z(g.npairs);
   for (int q = 0; q < g.npairs; ++q) z[q] = ring_geometry(g.nside, 2 * g.nside - q).z;
 
-  DevMem& M = g.mem;
+  // handed to the geometry when all is made: plans of other types keep it after a failure here
+  DevMem M;
   double* dz = nullptr;
   int32_t* dstart = nullptr;
   int rc;
@@ -623,6 +624,8 @@ int build_leg64(Geometry& g, const Reach& reach) {
   L.batch_from = batch_from;
   if (!ib.empty() && (rc = make_list(L.ana_batch, ib, wg_batch, FP64_BATCH_WAVES, g.ring_block_ana))) return rc;
   MWF_HIP(hipStreamSynchronize(nullptr));
+  g.mem.ptrs.insert(g.mem.ptrs.end(), M.ptrs.begin(), M.ptrs.end());
+  M.ptrs.clear();
   g.leg64 = L;
   g.leg64_ready = true;
   return WF_OK;
