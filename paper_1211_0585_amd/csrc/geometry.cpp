@@ -426,8 +426,8 @@ void one_map_shape(size_t items, int n_cu, int max_waves, int* nwg, int* waves) 
 // least-loaded workgroup, which keeps that order. off: the item range of each workgroup.
 // In a full launch the items of eight consecutive m go to the workgroups of one XCD (workgroup b
 // runs on XCD b mod 8): their 32-byte entries of G and F share 128-byte lines, which then are
-// fetched into one L2 and written back from one (Nside 512: analysis 107 -> 102 us, synthesis
-// 75 -> 69 us).
+// fetched into one L2 and written back from one (Nside 512: analysis 121 -> 116 us, synthesis
+// 93 -> 91 us).
 std::vector<Item64> pack_items(const std::vector<Item64>& items, const std::vector<int64_t>& cost, int nwg,
                                std::vector<int32_t>* off) {
   const int nx = nwg % 8 == 0 && nwg >= 64 ? 8 : 1;

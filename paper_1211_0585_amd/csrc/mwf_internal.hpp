@@ -396,9 +396,9 @@ inline size_t ring_lds_bytes(int fft_len, size_t elem) {
   return b < 8192 ? 8192 : b;
 }
 
-// cls: NRING_CLASSES classes, launched in order (empty ones skipped).
 // Zero `bytes` (a multiple of 16, 16-byte aligned) at p on s with a kernel.
 hipError_t launch_zero_fill(void* p, size_t bytes, hipStream_t s);
+// cls: NRING_CLASSES classes, launched in order (empty ones skipped).
 hipError_t launch_phase_b(const PlanDev& P, const PhaseBArgs& a, const RingClass* cls, bool fp32, hipStream_t s);
 // Every ring pair in one launch, transforms of any kind up to RING_ONE_LAUNCH points: 256 threads a pair up
 // to 2048 points, 512 above.

@@ -37,8 +37,9 @@
 // Work items are (m, block of 64 R ring pairs, range of l), one wavefront each; a lane owns R
 // ring pairs. An item starts from a recurrence state made at plan time, so its seeds cost a
 // load, it can start anywhere in l, and the l at which every ring of the block is still below
-// 2^-128 (m well above l sin(theta)) are not generated, summed or written at all (12 to 20 %
-// of the steps). The analysis splits a block's l into several items, since their outputs are
+// 2^-128 (m well above l sin(theta)) are not generated, summed or written at all: of the steps, 10 %
+// in the analysis and 12 % in the synthesis at Nside 512, lmax 1024 (blocks of 256 and 128 pairs), 14 % at
+// Nside 1024, lmax 2048, none at Nside 64, lmax 191. The analysis splits a block's l into several items, since their outputs are
 // independent: with one item per (m, block) at Nside 512, 3500 items for 3072 waves, the
 // longest set the launch's time (1.67 of the mean). A batch, whose maps fill the chip together, takes
 // longer items where one map's are short. The synthesis sums over l and takes smaller
@@ -54,11 +55,13 @@
 // LDS once per chunk of 16 values of l and writes one partial sum per block; a small kernel sums
 // the partials of each (l, m), applies the filter and forms the synthesis coefficients.
 //
-// One map, Nside 512, lmax 1024: analysis 136 -> 104 us, synthesis 102 -> 75 us; Nside 1024,
-// lmax 2048: 977 -> 672 and 748 -> 466 us; Nside 64, lmax 191: synthesis 10.9 -> 6.9 us. At
-// Nside 1024 the synthesis issues FP64 at four fifths of the rate a chain of independent FMAs
-// reaches with as many waves; the analysis loses another tenth to its reductions, and at Nside
-// 512 an item's set-up (ring states and S/D, 256 rows of G apart) weighs more.
+// Kernel times for one map, one wave per packed bin of whole blocks -> now: Nside 512, lmax 1024
+// analysis 145 -> 116 us, synthesis 110 -> 91 us; Nside 1024, lmax 2048 891 -> 687 and 687 -> 512 us;
+// Nside 64, lmax 191 16 -> 6.0 and 10.5 -> 6.5 us. FP64 issue bounds both: at Nside 1024 the items run
+// 3.42e9 (l, m, ring pair) units of four FP64 instructions (one multiply, three FMAs), which 1024 SIMDs
+// of 16 lanes could issue in 348 us at 2.4 GHz: 0.68 of the synthesis and 0.51 of the analysis, which
+// also sums over the lanes. At Nside 512 an item's set-up (ring states and S/D, 256 rows of G apart)
+// weighs more.
 #include <type_traits>
 
 #include "mwf_internal.hpp"

@@ -27,12 +27,14 @@
 // prime factor use Bluestein's chirp-z method: chirp, power-of-two FFT of length
 // M >= 2 n - 1, multiply by the plan-time filter spectrum, inverse FFT, chirp.
 // The FFT arithmetic type C is double for FP64 plans and float for plans that
-// store maps and ring coefficients in float. Ring pairs are launched in classes:
-// rings that are not a power of two (mixed radix and Bluestein) and power-of-two rings
+// store maps and ring coefficients in float. Few maps run all ring pairs in one launch, longest
+// transforms first, of 256 threads up to 2048 points and 512 up to 4096 (up to Nside 512; the bound on the maps
+// and the times of both are at Geometry::one_ring_launch). Otherwise ring pairs are launched in
+// classes: rings that are not a power of two (mixed radix and Bluestein) and power-of-two rings
 // separately (512 and 256 threads, LDS sized to the class: the Bluestein length is about
 // twice the ring's, and a mixed-radix ring counts twice its length; from 4 maps on, 256 threads
-// where those take at most 2048 points), and, from 4 maps on, transforms of at most 1024 points one wave per ring pair, so short polar
-// rings do not leave most of a large workgroup idle. Each workgroup stages the
+// where those take at most 2048 points), and, from 4 maps on, transforms of at most 1024 points one
+// wave per ring pair, so short polar rings do not leave most of a large workgroup idle. Each workgroup stages the
 // twiddles of its ring's transform in LDS next to the data, one table per pass
 // read by consecutive lanes at consecutive entries, and from 128 points on the data sit
 // in a padded layout between passes: both keep the passes' LDS accesses off shared banks.

@@ -86,7 +86,7 @@ struct Geometry {
   float2* blue32 = nullptr;
   double2* mixtw = nullptr;            // mixed-radix ring tables exp(-2 pi i t / n)
   float2* mixtw32 = nullptr;
-  // FP64 Legendre tables and work lists, made by the first FP64 or polarised plan of the shape
+  // FP64 Legendre work lists, made by the first FP64 or polarised plan of the shape
   bool leg64_ready = false;
   Leg64Dev leg64{};
   int n_cu = 0;                        // compute units of the device
@@ -103,12 +103,22 @@ struct Geometry {
   RingClass blue_split[2]{};
   // every ring pair, for one launch (count 0: the longest transform is over RING_ONE_LAUNCH points)
   RingClass ring_all{};
-  // One launch or one per class. One map: a sweep at Nside 16, 64, 128, 256 and 512 took 52, 54, 66, 96 and
-  // 250 us in launches by kind and takes 27, 32, 45, 76 and 244 us in one. 8 maps, FP64: 29, 50,
-  // 109, 417 and 1726 against 28, 47, 102, 363 and 1729 us. Beyond, the short rings' one-wave launch wins (64 maps
-  // at Nside 64: 128 against 169 us; 16 at Nside 512, FP32: 1423 against 1452), except where the longest
-  // transform is one of 2048 points, whose 256 threads suit nearly every ring: Nside 256, FP32, 16 maps
-  // 318 against 289 us, 24 maps 513 against 492, 64 maps 1124 against 1135.
+  // One launch or one per class: a sweep (us, lmax 2 nside) in launches per class / in one.
+  //   FP64, maps:           1           4           8          16          24          64
+  //   Nside 16          62/27       29/27       30/27       30/28       30/29       35/41
+  //   Nside 64          64/32       42/38       49/45       58/62       68/79     125/168
+  //   Nside 128         69/45       81/65      106/98     164/160     230/226     578/581
+  //   Nside 256        101/79     244/198     423/366     777/717   1127/1070   2925/2841
+  //   Nside 512       303/289     997/949   1869/1866   3620/3692   5383/5552 14681/15288
+  //   FP32
+  //   Nside 16          63/33       35/33       35/33       35/33       35/34       38/40
+  //   Nside 64          72/47       52/48       53/49       59/60       67/72      95/121
+  //   Nside 128         92/68       91/74      101/94     113/116     140/144     252/286
+  //   Nside 256       184/163     226/182     250/215     329/292     519/497   1128/1147
+  //   Nside 512       836/822     981/918   1113/1080   1463/1482   2396/2469   5270/5561
+  // Up to 8 maps one launch is never slower. Beyond, the short rings' one-wave launch wins sooner or later, last
+  // where the longest transform is one of 2048 points (Nside 256), whose 256 threads suit nearly every ring. (At
+  // Nside 16 to 128 one launch still gains 1 to 9 % up to 12 to 32 maps.)
   bool one_ring_launch(int nmaps) const { return ring_all.count && nmaps <= (ring_all.fft_len == 2048 ? 24 : 8); }
   // the batched class 0 (rings that are not a power of two, longer than SMALL_FFT) split the
   // same way for a plan's own launches: [0] the longest transforms, [1] the others at their
@@ -117,7 +127,7 @@ struct Geometry {
   DevMem mem;
 };
 
-// fp64: with the FP64 Legendre tables (leg64 and the bins).
+// fp64: with the FP64 Legendre work lists (leg64).
 int get_geometry(int nside, int lmax, bool fp64, std::shared_ptr<Geometry>* out);
 
 // One HEALPix ring (RING order, 1 <= i <= 4 nside - 1): z = cos(theta), first
