@@ -102,7 +102,7 @@ size_t plan_buffer_bytes(int nside, int lmax, int dtype, int nmaps) {
   const size_t el = dtype == WF_F64 ? 8 : 4;
   size_t b = 2 * (size_t)nmaps * npairs * gf_stride(lmax) * el + npix * el + (lmax + 1) * 8;
   if (dtype == WF_F64) {
-    const size_t rb = npairs <= 64 ? 64 : (npairs <= 128 ? 128 : 256);
+    const size_t rb = ana_ring_block((int)npairs);
     b += (size_t)nmaps * ((npairs + rb - 1) / rb) * nalm * 16 + (size_t)nmaps * rows * 16;
   } else {
     b += ((npairs + 127) / 128) * nalm * nmaps * 8 + rows * nmaps * 8;
@@ -121,13 +121,18 @@ size_t geometry_bytes(int nside, int lmax, bool fp64) {
       while (M < (size_t)(8 * i - 1)) M <<= 1;
       blue += M + 4 * i;
     }
-  // FP64 Legendre work lists: a start state per ring pair of every work item (at
-  // most one analysis item per (m, block) and 32 l, two per wave of a full launch beyond that; as many
-  // again for batches where one map's items are short)
-  const size_t nblk = (nside + 127) / 128, blocks = (size_t)(lmax + 1) * nblk;
-  const size_t ana = std::min<size_t>(5 * nalm / 16, blocks + 8192);
-  const size_t items = (nalm * nblk < (size_t)2 * FP64_BATCH_PART * 6144 ? 2 : 1) * ana + blocks;
-  const size_t leg64 = fp64 ? items * std::min(2 * nside + 63, 256) * 17 : 0;
+  // FP64 Legendre work lists: a start state per ring pair of every work item. Analysis (see
+  // build_leg64): one item per (m, block of ring pairs) and one more per 32 l, at most two per wave
+  // of a full launch (256 CUs); for batches, where one map's items are shorter than that, one per
+  // (m, block) and one more per FP64_BATCH_PART l. Synthesis: one per (m, block).
+  size_t leg64 = 0;
+  if (fp64) {
+    const size_t rb = ana_ring_block(2 * nside), nblk = (2 * nside + rb - 1) / rb;
+    const size_t blocks = (lmax + 1) * nblk, steps = nalm * nblk, full = 2 * FP64_ANA_WAVES * 256;
+    size_t items = 2 * blocks + std::min(steps / 32, full);
+    if (steps < FP64_BATCH_PART * full) items += blocks + steps / FP64_BATCH_PART;
+    leg64 = items * rb * 17;
+  }
   return 2 * rows * 8 + blue * 24 + (size_t)(lmax + 1) * 64 + (size_t)(16 * nside + 64) * 24 +
          5 * nalm + leg64 + 256 * 1024;
 }

@@ -54,8 +54,6 @@ void host_fft(std::vector<std::complex<long double>>& a, int sign) {
   }
 }
 
-int ana_ring_block(int npairs) { return npairs <= 64 ? 64 : (npairs <= 128 ? 128 : 256); }
-
 std::mutex g_geo_mu;
 // Weak entries: the tables of a shape live while a plan or serving lane holds them.
 std::map<std::tuple<int, int, int>, std::weak_ptr<Geometry>> g_geo;

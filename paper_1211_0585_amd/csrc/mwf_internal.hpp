@@ -82,6 +82,8 @@ constexpr int FP64_SYN_WAVES = 16;
 // Analysis of a batch: waves per workgroup and least l per item (see build_leg64).
 constexpr int FP64_BATCH_WAVES = 4;
 constexpr int FP64_BATCH_PART = 96;
+// Ring pairs per block of the FP64 analysis.
+inline int ana_ring_block(int npairs) { return npairs <= 64 ? 64 : (npairs <= 128 ? 128 : 256); }
 constexpr int FP64_SCALED_COST_ANA = 5;
 constexpr int FP64_SCALED_COST_SYN = 6;
 constexpr int FP64_ITEM_COST_L = 16;
