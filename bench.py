@@ -32,35 +32,42 @@ CON_FLOPS = 4               # one complex-by-real multiply-accumulate per (l, m,
 
 
 @functools.lru_cache(maxsize=None)
-def summed_units(np, nside, lmax):
+def summed_units(nside, lmax):
     """(l, m, ring pair) units that the FP64 Legendre sums cannot do without: from the l on at which
     |lambda_lm| of the pair's ring first exceeds 2^-128. The kernels leave earlier l out by blocks of ring
     pairs, so they run somewhat more than this (and less than the plan's units_active, which count
-    every l of a pair that leaves 2^-448)."""
-    i = np.arange(1, 2 * nside + 1, dtype=np.float64)
-    z = np.where(i < nside, 1.0 - i * i / (3.0 * nside * nside), 4.0 / 3.0 - 2.0 * i / (3.0 * nside))
-    m = np.arange(lmax + 1, dtype=np.float64)
+    every l of a pair that leaves 2^-448). On the host: seconds at Nside 512."""
+    import torch
+    i = torch.arange(1, 2 * nside + 1, dtype=torch.float64)
+    z = torch.where(i < nside, 1.0 - i * i / (3.0 * nside * nside), 4.0 / 3.0 - 2.0 * i / (3.0 * nside))
+    m = torch.arange(lmax + 1, dtype=torch.float64)
     # lambda = v 2^e, v kept below 2^64; norm_m^2 = (1 / 4 pi) prod (2 k + 1) / (2 k)
-    lognorm = 0.5 * np.cumsum(np.log2(np.concatenate([[1.0 / (4.0 * np.pi)], (2 * m[1:] + 1) / (2 * m[1:])])))
-    lg = (lognorm[:, None] + 0.5 * m[:, None] * np.log2((1.0 - z) * (1.0 + z))[None, :]).ravel()
-    e = np.floor(lg)
-    v, prev, eps = np.exp2(lg - e), np.zeros_like(lg), np.zeros_like(lg)
-    z, m = np.tile(z, lmax + 1), np.repeat(m, 2 * nside)
+    lognorm = 0.5 * torch.cumsum(torch.log2(torch.cat([m.new_full((1,), 1.0 / (4.0 * torch.pi)),
+                                                       (2 * m[1:] + 1) / (2 * m[1:])])), 0)
+    lg = (lognorm[:, None] + 0.5 * m[:, None] * torch.log2((1.0 - z) * (1.0 + z))[None, :]).reshape(-1)
+    e = torch.floor(lg)
+    v, prev = torch.exp2(lg - e), torch.zeros_like(lg)
+    z, mi = z.repeat(lmax + 1), torch.arange(lmax + 1).repeat_interleave(2 * nside)
+    floor = torch.exp2(-128.0 - e)            # of |v|, infinite far down
+    eps = torch.zeros_like(m)                 # of l - 1, by m
     units = 0
     for k in range(lmax + 1):                 # l = m + k of the pairs that have not risen so far
         if k:
             l = m + k
-            new = np.sqrt((l * l - m * m) / (4.0 * l * l - 1.0))
-            v, prev, eps = (z * v - eps * prev) / new, v, new
-        big = np.flatnonzero(np.abs(v) > 2.0 ** 64)
-        v[big] *= 2.0 ** -64
-        prev[big] *= 2.0 ** -64
-        e[big] += 64.0
-        risen = (e > -192.0) & (np.abs(v) > np.exp2(-128.0 - np.maximum(e, -192.0)))
-        units += int((lmax + 1 - m[risen] - k).sum())
-        on = ~risen & (m + k < lmax)
-        if not on.all():
-            z, m, v, prev, eps, e = z[on], m[on], v[on], prev[on], eps[on], e[on]
+            new = torch.sqrt((l * l - m * m) / (4.0 * l * l - 1.0))
+            v, prev, eps = z * (1.0 / new)[mi] * v - (eps / new)[mi] * prev, v, new
+        a = v.abs()
+        risen = a > floor
+        units += int((lmax + 1 - k - mi[risen]).clamp(min=0).sum())
+        v, prev = v.masked_fill(risen, 0.0), prev.masked_fill(risen, 0.0)      # counted: zero from here on
+        big = a > 2.0 ** 64
+        if big.any():
+            down = torch.where(big, 2.0 ** -64, 1.0)
+            v, prev, e = v * down, prev * down, e + 64.0 * big
+            floor = torch.exp2(-128.0 - e)
+        if k % 16 == 0:
+            on = (v != 0.0) & (mi + k < lmax)
+            z, mi, v, prev, e, floor = z[on], mi[on], v[on], prev[on], e[on], floor[on]
     return units
 
 
@@ -204,7 +211,7 @@ def main():
     ring_bytes_total = (32 * P * L1 + 16 * plan.npix                      # first sweep: G, d, q
                         + (K - 1) * (64 * P * L1 + 16 * plan.npix)        # F, G, d, q
                         + 32 * P * L1 + 8 * plan.npix)                    # final synthesis
-    units_summed = summed_units(np, nside, lmax)
+    units_summed = summed_units(nside, lmax)
     leg_flops = (REC_FLOPS + CON_FLOPS) * units_summed                    # per launch, one map
     kern = {
         "legendre_analysis": {"ms_avg": st.ms_analysis / max(st.n_analysis, 1),
@@ -469,7 +476,7 @@ def run_pol(args, np, torch, mwf, synth, dev):
     ring = st.ms_ring / max(st.n_ring, 1)
     # per (l, m, ring pair): spin-0 T 7 flops from the first l that counts on; spin-2 E/B analysis 24 (two
     # recurrences of two multiply-adds, eight multiply-adds into E and B), synthesis 26 (plus sum and difference)
-    t_flops = (REC_FLOPS + CON_FLOPS) * summed_units(np, nside, lmax)
+    t_flops = (REC_FLOPS + CON_FLOPS) * summed_units(nside, lmax)
     ana_flops = t_flops + 24 * units
     syn_flops = t_flops + 26 * units
     ring_bytes = 3 * 64 * 2 * nside * (lmax + 1) + (3 + 6) * 8 * 12 * nside * nside   # F, G of 3 fields; d, N^-1

@@ -16,4 +16,4 @@ def test_summed_units(nside, lmax):
         new = (np.abs(lam) > np.longdouble(2) ** -128) & (first[:, :l + 1] > lmax)
         first[:, :l + 1] = np.where(new, l - m, first[:, :l + 1])
     want = int(np.maximum(lmax + 1 - np.arange(lmax + 1) - first, 0).sum())
-    assert bench.summed_units(np, nside, lmax) == want
+    assert bench.summed_units(nside, lmax) == want
