@@ -30,3 +30,22 @@ def test_batch_analysis_equals_single_maps(nside, lmax, nmaps, tol):
             print(f"Nside {nside} lmax {lmax} map {i} of {nmaps}: {err:.2e}", flush=True)
             assert np.array_equal(whole[i], one) if tol == 0 else err <= tol
         p.sync()
+
+
+def test_polarised_batch_analysis_equals_single_maps():
+    """The spin-0 part of a polarised batch takes the same lists; its ring kernels do not depend on the count."""
+    import torch
+    from paper_1211_0585_amd import mwf
+    nside, lmax, nmaps = 128, 383, 6
+    npix = 12 * nside * nside
+    cl4 = np.zeros((4, lmax + 1))
+    cl4[:3, 2:] = 1.0
+    ninv6 = np.zeros((6, npix))
+    ninv6[:3] = 1.0
+    x = torch.randn(nmaps, 3, npix, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(7))
+    with mwf.PolPlan(nside, lmax, cl4, ninv6, max_batch=nmaps) as p:
+        whole = p.map2alm(x).cpu().numpy().reshape(nmaps, 3, -1)
+        for i in (0, nmaps - 1):
+            one = p.map2alm(x[i].contiguous()).cpu().numpy().reshape(3, -1)
+            assert np.array_equal(whole[i], one)
+        p.sync()
